@@ -112,6 +112,7 @@ pmc_store* store_from_meta(const pmc_field* f, const Geo& g, int n, const double
 // memory): pmc_ctx_create looks up its device address once per device with
 // hipGetSymbolAddress, and only that address is passed on.
 static_assert(PMC_STATIC_WS_BYTES % 256 == 0, "static workspace size");
+static_assert(kPinBytes >= kRangeGroups * kRangeWords * 8, "the pinned buffer holds every partial of the range");
 static_assert(kPinBytes >= kMaxComps * sizeof(CompMeta), "the pinned buffer holds every component's metadata");
 static __device__ __align__(256) uint8_t scratch[PMC_STATIC_WS_BYTES];
 
@@ -250,15 +251,32 @@ pmc_status pmc_range(pmc_ctx* ctx, const pmc_field* f, const void* d_x, void* d_
   if (!d_ws || ws_bytes < 256) return fail(ctx, PMC_E_NOMEM, "range needs 256 bytes of workspace");
   hipError_t e = hipSetDevice(ctx->device);
   if (e != hipSuccess) return hipfail(ctx, e, "hipSetDevice");
-  unsigned long long* w = (unsigned long long*)d_ws;
   const uint64_t n = g.nx * g.ny * g.nz;
-  // min key all ones; max key and non-finite count zero
-  if ((e = launch_fill64_one(w, 3, 0ull, 0, ~0ull, ctx->stream)) != hipSuccess) return hipfail(ctx, e, "fill");
-  if (f->dtype == PMC_F32) e = launch_range<float>((const float*)d_x, n, w, ctx->stream);
-  else e = launch_range<double>((const double*)d_x, n, w, ctx->stream);
+  // the workgroups' partials go straight to the context's pinned buffer (the
+  // device writes host memory), or into the workspace where there is none
+  void* dev_pin = nullptr;
+  if (!ctx->pin || hipHostGetDevicePointer(&dev_pin, ctx->pin, 0) != hipSuccess) dev_pin = nullptr;
+  const uint64_t part = kRangeWords * 8;
+  unsigned long long* w = (unsigned long long*)(dev_pin ? dev_pin : d_ws);
+  const uint32_t groups = range_groups(n, (dev_pin ? kPinBytes : ws_bytes) / part);
+  if (f->dtype == PMC_F32) e = launch_range<float>((const float*)d_x, n, w, groups, ctx->stream);
+  else e = launch_range<double>((const double*)d_x, n, w, groups, ctx->stream);
   if (e != hipSuccess) return hipfail(ctx, e, "range kernel");
-  unsigned long long h[3];
-  if ((e = read_back(ctx, h, w, sizeof(h))) != hipSuccess) return hipfail(ctx, e, "range read");
+  std::vector<unsigned long long> hp;
+  const unsigned long long* p = (const unsigned long long*)ctx->pin;
+  if (!dev_pin) {
+    hp.resize(kRangeWords * (size_t)groups);
+    p = hp.data();
+    e = hipMemcpyAsync(hp.data(), w, groups * part, hipMemcpyDeviceToHost, ctx->stream);
+  }
+  if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+  if (e != hipSuccess) return hipfail(ctx, e, "range read");
+  unsigned long long h[3] = {~0ull, 0ull, 0ull};
+  for (uint32_t i = 0; i < groups; ++i) {
+    h[0] = std::min(h[0], p[kRangeWords * i]);
+    h[1] = std::max(h[1], p[kRangeWords * i + 1]);
+    h[2] += p[kRangeWords * i + 2];
+  }
   auto unorder = [](unsigned long long o) {
     uint64_t b = (o >> 63) ? (o & 0x7FFFFFFFFFFFFFFFull) : ~o;
     double v;

@@ -196,7 +196,13 @@ hipError_t launch_decode(const DecArgs<T>& a, uint64_t max_span, int codec, bool
 template <class T>
 hipError_t launch_decode_box(const DecArgs<T>& a, const BoxArgs& b, uint64_t max_span, int codec, hipStream_t s);
 uint64_t stage_words();  // capacity of the decoder's LDS staging buffer, in words
-template <class T> hipError_t launch_range(const T* x, uint64_t n, unsigned long long* out, hipStream_t s);
+// min / max / non-finite count of n samples: one partial of kRangeWords words
+// per workgroup at out; range_groups: how many workgroups suit n, at most
+// max_groups
+constexpr uint32_t kRangeWords = 3, kRangeGroups = 256;
+uint32_t range_groups(uint64_t n, uint64_t max_groups);
+template <class T>
+hipError_t launch_range(const T* x, uint64_t n, unsigned long long* out, uint32_t groups, hipStream_t s);
 hipError_t launch_fill64(unsigned long long* p, uint64_t n, unsigned long long v, hipStream_t s);
 // the same with p[j] = vj instead (one launch)
 hipError_t launch_fill64_one(unsigned long long* p, uint64_t n, unsigned long long v, uint64_t j,
