@@ -11,12 +11,13 @@ import os
 import shutil
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpmc.so")
-SOURCES = ["kernels.hip", "capi.cpp", "batch.cpp", "server.cpp", "format.cpp"]
+SOURCES = ["kernels.hip", "decode_f32.hip", "decode_f64.hip", "capi.cpp", "batch.cpp", "server.cpp", "format.cpp"]
 ARCH = os.environ.get("PMC_OFFLOAD_ARCH", "gfx950")
 
 
@@ -34,10 +35,10 @@ def flags():
 
 
 def build(verbose=False, extra=()):
-    objs = []
     tmpdir = os.path.join(HERE, "_build")
     os.makedirs(tmpdir, exist_ok=True)
-    for src in SOURCES:
+
+    def compile_one(src):
         obj = os.path.join(tmpdir, src + ".o")
         cmd = [hipcc()] + flags() + list(extra) + ["-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
@@ -48,7 +49,11 @@ def build(verbose=False, extra=()):
             raise RuntimeError("hipcc failed for %s:\n%s" % (src, err))
         if verbose and err.strip():
             print(err, file=sys.stderr)
-        objs.append(obj)
+        return obj
+
+    # the sources are independent, and the kernels take minutes
+    with ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 1)) as ex:
+        objs = list(ex.map(compile_one, SOURCES))
     tmp = LIB + ".tmp%d" % os.getpid()
     cmd = [hipcc(), "-shared", "-fPIC", "--offload-arch=" + ARCH, "-o", tmp] + objs
     r = subprocess.run(cmd, capture_output=True, text=True)

@@ -1,0 +1,265 @@
+// block_device.hpp -- device helpers around one 4x4x4 block per lane: its place
+// in the field, gather and scatter with edge replication, error maxima.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include <type_traits>
+
+#include "codec_device.hpp"
+#include "launch.hpp"
+
+namespace pmc {
+
+typedef __attribute__((address_space(3))) void lds_void_t;
+typedef __attribute__((address_space(1))) const void gmem_void_t;
+
+// ---------------------------------------------------------------------------
+// block gather / scatter with edge replication for partial blocks
+struct BlockPos {
+  uint64_t x0, y0, z0;
+  uint32_t vx, vy, vz;  // valid extents (1..4)
+};
+
+__device__ __forceinline__ BlockPos block_pos(const Geo& g, uint64_t blk) {
+  BlockPos b;
+  uint64_t bx = blk % g.nbx;
+  uint64_t t = blk / g.nbx;
+  uint64_t by = t % g.nby;
+  uint64_t bz = t / g.nby;
+  b.x0 = 4 * bx;
+  b.y0 = 4 * by;
+  b.z0 = 4 * bz;
+  b.vx = (uint32_t)min<uint64_t>(4, g.nx - b.x0);
+  b.vy = (uint32_t)min<uint64_t>(4, g.ny - b.y0);
+  b.vz = (uint32_t)min<uint64_t>(4, g.nz - b.z0);
+  return b;
+}
+
+__device__ __forceinline__ bool lvalid(const BlockPos& b, int l) {
+  return (uint32_t)(l & 3) < b.vx && (uint32_t)((l >> 2) & 3) < b.vy && (uint32_t)(l >> 4) < b.vz;
+}
+// bit l set when sample l of the block lies inside the field
+__device__ __forceinline__ uint64_t valid_mask(const BlockPos& b) {
+  const uint64_t xm = (1ull << b.vx) - 1ull;                                               // a row
+  const uint64_t ym = (xm | xm << 4 | xm << 8 | xm << 12) & ((1ull << (4 * b.vy)) - 1ull);  // a z slice
+  const uint64_t zm = ym | ym << 16 | ym << 32 | ym << 48;
+  return b.vz == 4 ? zm : zm & ((1ull << (16 * b.vz)) - 1ull);
+}
+// |v| for sample l, or +0 where the sample lies outside the field: the mask
+// bit becomes an all-ones / all-zeros word applied to the double's bits, so
+// no per-sample condition (a lane mask) has to stay live
+__device__ __forceinline__ double masked_abs(uint64_t m, int l, double v) {
+  const uint64_t keep = 0ull - ((m >> l) & 1ull);
+  return __longlong_as_double((long long)((uint64_t)__double_as_longlong(v) & keep & 0x7FFFFFFFFFFFFFFFull));
+}
+
+// one block row (ly, lz): 4 consecutive x values; rows of partial blocks
+// repeat their last valid sample (edge replication on load)
+template <class T>
+__device__ __forceinline__ const T* row_ptr(const T* f, const Geo& g, const BlockPos& b, int r) {
+  const uint32_t ly = min<uint32_t>(r & 3, b.vy - 1), lz = min<uint32_t>(r >> 2, b.vz - 1);
+  return f + b.x0 + g.nx * ((b.y0 + ly) + g.ny * (b.z0 + lz));
+}
+
+// A full block's rows start at block_base + row_step(r): the step depends only
+// on the field's shape, so it is the same for every lane (scalar registers)
+// and a lane keeps one address instead of one per row.
+template <class T> __device__ __forceinline__ T* block_base(T* f, const Geo& g, const BlockPos& b) {
+  return f + (b.x0 + g.nx * (b.y0 + g.ny * b.z0));
+}
+__device__ __forceinline__ uint64_t row_step(const Geo& g, int r) {
+  return g.nx * (uint64_t)(r & 3) + g.nx * g.ny * (uint64_t)(r >> 2);
+}
+
+template <class T>
+__device__ __forceinline__ void load_block(const T* __restrict__ f, const Geo& g, const BlockPos& b, T v[64]) {
+  const bool vec = b.vx == 4 && g.rows_aligned;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const T* row = row_ptr(f, g, b, r);
+    if (vec) {
+      if constexpr (sizeof(T) == 4) {
+        float4 q = *reinterpret_cast<const float4*>(row);
+        v[4 * r] = q.x; v[4 * r + 1] = q.y; v[4 * r + 2] = q.z; v[4 * r + 3] = q.w;
+      } else {
+        double2 q0 = *reinterpret_cast<const double2*>(row);
+        double2 q1 = *reinterpret_cast<const double2*>(row + 2);
+        v[4 * r] = q0.x; v[4 * r + 1] = q0.y; v[4 * r + 2] = q1.x; v[4 * r + 3] = q1.y;
+      }
+    } else {
+      const uint32_t m = b.vx - 1;
+      v[4 * r] = row[0];
+      v[4 * r + 1] = row[min<uint32_t>(1, m)];
+      v[4 * r + 2] = row[min<uint32_t>(2, m)];
+      v[4 * r + 3] = row[min<uint32_t>(3, m)];
+    }
+  }
+}
+
+// one 16-byte row piece written with the streaming (nt) cache policy: the
+// partial sums a launch writes are read back only by a later launch, after far
+// more than the L2 holds has passed through it, so keeping them in L2 would
+// only push out lines this launch still reads
+typedef float nt_f4 __attribute__((ext_vector_type(4)));
+typedef double nt_d2 __attribute__((ext_vector_type(2)));
+template <class T>
+__device__ __forceinline__ void store_row16_nt(T* row, T a, T b, T c, T d) {
+  if constexpr (sizeof(T) == 4) {
+    __builtin_nontemporal_store(nt_f4{a, b, c, d}, reinterpret_cast<nt_f4*>(row));
+  } else {
+    __builtin_nontemporal_store(nt_d2{a, b}, reinterpret_cast<nt_d2*>(row));
+    __builtin_nontemporal_store(nt_d2{c, d}, reinterpret_cast<nt_d2*>(row + 2));
+  }
+}
+
+template <class T>
+__device__ __forceinline__ void store_block(T* __restrict__ f, const Geo& g, const BlockPos& b, const T v[64]) {
+  const bool vec = b.vx == 4 && g.rows_aligned;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    if ((uint32_t)(r & 3) >= b.vy || (uint32_t)(r >> 2) >= b.vz) continue;
+    T* row = const_cast<T*>(row_ptr((const T*)f, g, b, r));
+    if (vec) {
+      store_row16_nt(row, v[4 * r], v[4 * r + 1], v[4 * r + 2], v[4 * r + 3]);
+    } else {
+      row[0] = v[4 * r];
+      if (b.vx > 1) row[1] = v[4 * r + 1];
+      if (b.vx > 2) row[2] = v[4 * r + 2];
+      if (b.vx > 3) row[3] = v[4 * r + 3];
+    }
+  }
+}
+
+// store row r of a block (valid samples only); wfull: every lane of the wave
+// has a full block of aligned rows (a wave-uniform flag), so the store needs
+// no per-lane path
+template <class T>
+__device__ __forceinline__ void store_row(T* __restrict__ f, const Geo& g, const BlockPos& b, int r, const T v[4],
+                                          bool wfull = false) {
+  if (!wfull && ((uint32_t)(r & 3) >= b.vy || (uint32_t)(r >> 2) >= b.vz)) return;
+  T* row = wfull ? block_base(f, g, b) + row_step(g, r) : const_cast<T*>(row_ptr((const T*)f, g, b, r));
+  if (wfull || (b.vx == 4 && g.rows_aligned)) {
+    store_row16_nt(row, v[0], v[1], v[2], v[3]);
+  } else {
+    row[0] = v[0];
+    if (b.vx > 1) row[1] = v[1];
+    if (b.vx > 2) row[2] = v[2];
+    if (b.vx > 3) row[3] = v[3];
+  }
+}
+
+// the samples of a block that lie in a box, read from / written to the box's
+// own dense array (x fastest); samples outside the field are outside every
+// box, and samples of the block outside the box are not touched (read as +0)
+template <class T>
+__device__ __forceinline__ void load_box(const T* __restrict__ f, const BoxArgs& bx, const BlockPos& b, T v[64]) {
+  const uint64_t nx = bx.hi[0] - bx.lo[0], ny = bx.hi[1] - bx.lo[1];
+#pragma unroll
+  for (int l = 0; l < 64; ++l) {
+    const uint64_t x = b.x0 + (l & 3), y = b.y0 + ((l >> 2) & 3), z = b.z0 + (l >> 4);
+    v[l] = (x >= bx.lo[0] && x < bx.hi[0] && y >= bx.lo[1] && y < bx.hi[1] && z >= bx.lo[2] && z < bx.hi[2])
+               ? f[(x - bx.lo[0]) + nx * ((y - bx.lo[1]) + ny * (z - bx.lo[2]))]
+               : (T)0;
+  }
+}
+template <class T>
+__device__ __forceinline__ void store_box(T* __restrict__ f, const BoxArgs& bx, const BlockPos& b, const T v[64]) {
+  const uint64_t nx = bx.hi[0] - bx.lo[0], ny = bx.hi[1] - bx.lo[1];
+#pragma unroll
+  for (int l = 0; l < 64; ++l) {
+    const uint64_t x = b.x0 + (l & 3), y = b.y0 + ((l >> 2) & 3), z = b.z0 + (l >> 4);
+    if (x >= bx.lo[0] && x < bx.hi[0] && y >= bx.lo[1] && y < bx.hi[1] && z >= bx.lo[2] && z < bx.hi[2])
+      f[(x - bx.lo[0]) + nx * ((y - bx.lo[1]) + ny * (z - bx.lo[2]))] = v[l];
+  }
+}
+
+// load row r of a block (edge replication as in load_block); a null field
+// reads as +0
+template <class T>
+__device__ __forceinline__ void load_row(const T* f, const Geo& g, const BlockPos& b, int r, T v[4]) {
+  if (!f) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) v[t] = (T)0;
+    return;
+  }
+  const T* row = row_ptr(f, g, b, r);
+  if (b.vx == 4 && g.rows_aligned) {
+    if constexpr (sizeof(T) == 4) {
+      float4 q = *reinterpret_cast<const float4*>(row);
+      v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
+    } else {
+      double2 q0 = *reinterpret_cast<const double2*>(row);
+      double2 q1 = *reinterpret_cast<const double2*>(row + 2);
+      v[0] = q0.x; v[1] = q0.y; v[2] = q1.x; v[3] = q1.y;
+    }
+  } else {
+    const uint32_t m = b.vx - 1;
+    v[0] = row[0];
+    v[1] = row[min<uint32_t>(1, m)];
+    v[2] = row[min<uint32_t>(2, m)];
+    v[3] = row[min<uint32_t>(3, m)];
+  }
+}
+
+// rows [r0, r0 + R) of a block into v[4R].  When every lane of the wave has a
+// full block of aligned rows (wfull, a wave-uniform flag) the R loads are
+// plain 16-byte loads at the block base plus a uniform step, with no per-lane
+// branch, so they are all in flight together; otherwise each row takes
+// load_row's per-lane path.  A null field reads as +0.
+template <class T, int R>
+__device__ __forceinline__ void load_rows(const T* f, const Geo& g, const BlockPos& b, int r0, bool wfull,
+                                          T v[4 * R]) {
+  if (!f) {
+#pragma unroll
+    for (int k = 0; k < 4 * R; ++k) v[k] = (T)0;
+    return;
+  }
+  if (wfull) {
+    const T* const base = block_base(f, g, b);
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      const T* row = base + row_step(g, r0 + k);
+      if constexpr (sizeof(T) == 4) {
+        const float4 q = *reinterpret_cast<const float4*>(row);
+        v[4 * k] = q.x; v[4 * k + 1] = q.y; v[4 * k + 2] = q.z; v[4 * k + 3] = q.w;
+      } else {
+        const double2 q0 = *reinterpret_cast<const double2*>(row);
+        const double2 q1 = *reinterpret_cast<const double2*>(row + 2);
+        v[4 * k] = q0.x; v[4 * k + 1] = q0.y; v[4 * k + 2] = q1.x; v[4 * k + 3] = q1.y;
+      }
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < R; ++k) load_row(f, g, b, r0 + k, v + 4 * k);
+  }
+}
+
+
+__device__ __forceinline__ BlockPos opaque_pos(BlockPos b) {
+  b.x0 = opaque(b.x0);
+  b.y0 = opaque(b.y0);
+  b.z0 = opaque(b.z0);
+  return b;
+}
+
+// a + v * scale where v * scale is exact: one fused multiply-add equals the
+// plain sum of the (exact) product
+__device__ __forceinline__ float fma_exact(float v, float scale, float a) { return __builtin_fmaf(v, scale, a); }
+__device__ __forceinline__ double fma_exact(double v, double scale, double a) { return a + v * scale; }
+
+// NaN-propagating max, matching "take a if not a <= m"
+__device__ __forceinline__ double nmax(double m, double a) { return a <= m ? m : a; }
+// the same maximum where no operand is NaN: one v_max_f64 instead of a
+// compare and two selects.  The candidate checks take it: |x - x~_i| with
+// x finite (an input with NaN or Inf fails the call whatever its streams)
+// and x~_i finite or, on overflow, infinite (x~_{i-1} stays within tau of x)
+__device__ __forceinline__ double nmax_num(double m, double a) { return __builtin_fmax(m, a); }
+
+__device__ __forceinline__ double wave_max(double v) {
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) v = nmax(v, __shfl_xor(v, d, 64));
+  return v;
+}
+
+}  // namespace pmc

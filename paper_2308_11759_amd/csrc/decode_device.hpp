@@ -1,0 +1,464 @@
+// decode_device.hpp -- the retrieval kernels (Alg. 2) and their launchers,
+// instantiated per element type by decode_f32.hip and decode_f64.hip.
+//
+//  k_decode          components [k0, k1) of a field added left to right into
+//                    x~; one lane per block, located by the chunk index plus a
+//                    per-block bit offset written by the encoder
+//  k_decode_box      the blocks meeting a box, written as the box alone
+//  k_decode_queries  many retrievals in one launch
+#pragma once
+#include "block_device.hpp"
+
+namespace pmc {
+
+// ---------------------------------------------------------------------------
+// Alg. 2 over one block per lane: x~ = (((x~_in or +0) + x_1) + x_2) ... in
+// the field precision; the block's bits start at its chunk's word offset plus
+// the block's bit offset from the per-block index
+// routes of the inverse transform: kRouteAuto picks per wave (float64: the
+// high-word route where it applies); kRouteFull the plain route; kRouteHi16
+// the float32 high-half route, for components whose every block has p <= 10
+// and fast_dequant(emax) (the caller guarantees it)
+constexpr int kRouteAuto = 0, kRouteFull = 1, kRouteHi16 = 2;
+template <class T, int kRoute = kRouteAuto, class R>
+__device__ __forceinline__ bool decode_block_add(R& r, int minexp, T acc[64], const uint8_t* sq, bool rel) {
+  typedef typename FT<T>::U U;
+  constexpr int P = FT<T>::P;
+  constexpr int EB = FT<T>::EBITS;
+  const uint32_t h = r.peek32();
+  if (!(h & 1u)) {  // empty: x_i = 0 leaves x~ unchanged
+    r.skip(1);
+    return true;
+  }
+  if (h & 2u) {  // raw block
+    r.skip(2);
+#pragma unroll
+    for (int l = 0; l < 64; ++l) {
+      T v = from_raw((U)r.get64((uint32_t)P), (T)0);
+      acc[l] = acc[l] + v;
+    }
+    return true;
+  }
+  // unary escalation count, then the biased block exponent
+  int delta = (int)__builtin_ctz(~(h >> 2) | 0x40000000u);
+  int emax;
+  if (3 + delta + EB <= 32) {
+    emax = (int)((h >> (3 + delta)) & ((1u << EB) - 1u)) - FT<T>::BIAS;
+    r.skip((uint32_t)(3 + delta + EB));
+  } else {
+    r.skip(2);
+    delta = 0;
+#pragma unroll 1
+    while (r.get(1)) {  // (rare: a long escalation; kept as a loop)
+      if (++delta > P) return false;
+    }
+    emax = (int)r.get((uint32_t)EB) - FT<T>::BIAS;
+  }
+  int p = emax - minexp + kGuard;
+  p = (p < 0 ? 0 : (p > P ? P : p)) + delta;
+  if (emax < 2 - FT<T>::BIAS || p < 1 || p > P) return false;
+  // Leading empty planes: until a coefficient is significant, a plane
+  // without a new one is a single 0 (its negative group test), so the first
+  // zeros of the block's plane data are that many empty planes, skipped at once.
+  const int z0 = (int)__builtin_ctz(r.peek32() | 0x80000000u);
+  const int zlead = z0 < p ? z0 : p;
+  r.skip((uint32_t)zlead);
+  if constexpr (sizeof(T) == 8 && kRoute == kRouteAuto) {
+    // residual components whose coded planes all lie in the top ten bit
+    // positions and keep every result normal: the lifting on the words' top
+    // 16 bits, two per register, from 4 or 8 slots (wave-uniform choices)
+    if (rel && __all(p <= 10 && emax >= -1008)) {
+      const int np = p - zlead;
+      v2s R2[32];
+      if (__all(np <= 4)) {
+        slots_hi16<4>(r, p, zlead, sq, R2);
+        lift_dequant_add_hi16(R2, emax, acc);
+        return true;
+      }
+      if (__all(np <= 8)) {
+        slots_hi16<8>(r, p, zlead, sq, R2);
+        lift_dequant_add_hi16(R2, emax, acc);
+        return true;
+      }
+    }
+    // every coded plane in the top 26 bit positions and every result
+    // normal: the lifting on the coefficients' high words (a wave-uniform
+    // choice; both routes give the same sums)
+    if (__all(p <= 26 && emax >= -992)) {
+      const int np = p - zlead;
+      if (__all(np <= 4)) decode_hi32<4>(r, p, zlead, emax, acc, sq, rel);
+      else if (__all(np <= 8)) decode_hi32<8>(r, p, zlead, emax, acc, sq, rel);
+      else decode_hi32<16>(r, p, zlead, emax, acc, sq, rel);
+      return true;
+    }
+  }
+  if constexpr (sizeof(T) == 4 && kRoute == kRouteHi16) {
+    // residual components (rel): the packed pairs straight from 4 or 8
+    // slots, else from the 32-bit words of 16
+    v2s R2[32];
+    const int np = p - zlead;
+    if (__all(np <= 4)) {
+      slots_hi16<4>(r, p, zlead, sq, R2);
+    } else if (__all(np <= 8)) {
+      slots_hi16<8>(r, p, zlead, sq, R2);
+    } else {
+      typename FT<T>::S c[64];
+      planes_slots<T, 16>(r, c, p, zlead, sq, rel);
+      pack_hi16(c, R2);
+    }
+    lift_dequant_add_hi16(R2, emax, acc);
+    return true;
+  }
+  typename FT<T>::S c[64], q[64];
+  planes_read<T>(r, c, p, zlead, sq, rel);
+  inverse_zy_ints<T>(c, q);
+  inverse_x<T>(q);
+  dequant_add(q, emax, acc);
+  return true;
+}
+
+// words of one wave's four chunks staged in LDS per component (13.3 KB, so
+// that 12 one-wave workgroups fit a CU's LDS); spans larger than this use
+// the global-memory reader (the host picks the variant from the largest span
+// of the streams it decodes)
+constexpr uint32_t kStageWords = 3326;
+// The staging buffer is double-buffered while spans are small: two halves of
+// kHalfWords data words (64-word multiples, since a copy writes whole 64-word
+// rows) plus 3 spare words each for the reader's look-ahead.  The next
+// component's words load into one half while the wave decodes from the other.
+// A component whose span exceeds a half uses the whole buffer and is staged
+// without overlap.
+constexpr uint32_t kHalfWords = 1600;
+constexpr uint32_t kHalf1 = kHalfWords + 3;  // word offset of the second half
+static_assert(kHalf1 + kHalfWords + 3 <= kStageWords + 3, "halves fit the buffer");
+
+// the wave's span of payload words of one component: its chunks [4w, 4w + 4)
+// are consecutive in the payload
+struct Span {
+  uint64_t s0, s1;
+  bool ok;
+};
+__device__ __forceinline__ Span wave_span(const uint32_t* index, uint64_t nchunks, uint64_t words, uint64_t w) {
+  const uint64_t c0 = w * 4, c1 = min<uint64_t>(c0 + 4, nchunks);
+  Span sp;
+  sp.s0 = index[c0];
+  sp.s1 = c1 < nchunks ? (uint64_t)index[c1] : words;
+  sp.ok = sp.s0 <= sp.s1 && sp.s1 <= words && sp.s1 - sp.s0 <= kStageWords;
+  return sp;
+}
+// issue (not wait for) the copy of a span into the staging words at `base`
+__device__ __forceinline__ void stage_span(const uint32_t* payload, const Span& sp, uint32_t* stage, uint32_t base) {
+  const uint32_t lane = threadIdx.x;
+  const uint32_t span = (uint32_t)(sp.s1 - sp.s0);
+  for (uint32_t k = 0; k < span; k += 64) {
+    const uint32_t j = k + lane < span ? k + lane : span - 1;
+    __builtin_amdgcn_global_load_lds((gmem_void_t*)(payload + sp.s0 + j), (lds_void_t*)(stage + base + k), 4, 0, 0);
+  }
+}
+
+// decode the wave's 64 blocks [64 w, 64 w + 64) of a field: x~ = in (or +0)
+// plus components [0, ncomp) of the given streams, left to right.  Every lane
+// runs the component loop (the staging copies are shared); false on a
+// malformed stream.  kFull: every block of the field is full and rows are
+// aligned (all dimensions multiples of 4): no per-lane edge paths.
+// one block of one component, codec 0 (minexp) or codec 1 (step = 2 tau)
+template <class T, int kCodec, int kRoute = kRouteAuto, class R>
+__device__ __forceinline__ bool decode_block_codec(R& r, int minexp, double step, T acc[64], const uint8_t* sq,
+                                                   bool rel) {
+  if constexpr (kCodec == 0) return decode_block_add<T, kRoute>(r, minexp, acc, sq, rel);
+  else return pq_decode_add<T>(r, step, acc);
+}
+
+template <class T, bool kStaged, bool kBox = false, bool kFull = false, int kCodec = 0, bool kHiRes = false>
+__device__ __forceinline__ bool decode_wave(const Geo& g, const uint8_t* const* s, const uint32_t* const* aux,
+                                            const uint64_t* words, const int* minexp, const double* step, int ncomp,
+                                            uint32_t relmask, const T* in, T* out, uint64_t w, const uint8_t* sq,
+                                            uint32_t* stage, const BoxArgs* box = nullptr) {
+  const uint32_t lane = threadIdx.x;
+  const uint64_t blk = w * 64 + lane;
+  bool active = blk < g.nblocks;
+  BlockPos bp = block_pos(g, active ? blk : 0);
+  if constexpr (kFull) {
+    bp.vx = 4;
+    bp.vy = 4;
+    bp.vz = 4;
+  }
+  if constexpr (kBox) {  // only this row's blocks in the box are decoded (each by
+                         // one workgroup); the wave still stages its chunks,
+                         // whose bit offsets locate every block
+    active = active && blk >= box->row_first && blk <= box->row_last;
+  }
+  const uint64_t chunk = blk / kChunkBlocks;
+  T acc[64];
+  if (in && active) {
+    if constexpr (kBox) load_box(in, *box, bp, acc);
+    else if constexpr (kFull) load_rows<T, 16>(in, g, opaque_pos(bp), 0, true, acc);
+    else load_block(in, g, opaque_pos(bp), acc);
+  } else {
+#pragma unroll
+    for (int l = 0; l < 64; ++l) acc[l] = (T)0;
+  }
+  bool ok = true;
+  if constexpr (kStaged) {
+    // component i: its span, where it sits in LDS, and this lane's chunk range
+    // and bit offset (loaded together with the span's words)
+    Span cur{0, 0, false};
+    uint32_t cur_base = 0, cur_cap = kStageWords;
+    uint32_t start = 0, stop = 0, off = 0;  // word offsets (a payload has < 2^32 words) and bit offset
+    if (ncomp > 0) {
+      const uint32_t* index = reinterpret_cast<const uint32_t*>(s[0] + kHeaderBytes);
+      cur = wave_span(index, g.nchunks, words[0], w);
+      cur_cap = cur.s1 - cur.s0 <= kHalfWords ? kHalfWords : kStageWords;
+      if (cur.ok) stage_span(index + g.nchunks, cur, stage, 0);
+      if (active) {
+        start = index[chunk];
+        stop = chunk + 1 < g.nchunks ? index[chunk + 1] : (uint32_t)min<uint64_t>(words[0], 0xFFFFFFFFull);
+        off = aux[0][blk];
+      }
+    }
+    auto component = [&](int i, auto route) {
+        __builtin_amdgcn_s_waitcnt(0);  // component i's words and lane values
+        __syncthreads();
+        // the next component: into the other half while this one decodes, when
+        // both fit a half
+        Span nxt{0, 0, false};
+        uint32_t nxt_base = 0, nxt_cap = kStageWords;
+        uint32_t nstart = 0, nstop = 0, noff = 0;
+        bool pre = false;
+        const uint32_t* nindex = nullptr;
+        if (i + 1 < ncomp) {
+          nindex = reinterpret_cast<const uint32_t*>(s[i + 1] + kHeaderBytes);
+          nxt = wave_span(nindex, g.nchunks, words[i + 1], w);
+          pre = nxt.ok && cur.ok && cur.s1 - cur.s0 <= kHalfWords && nxt.s1 - nxt.s0 <= kHalfWords;
+          if (pre) {
+            nxt_base = cur_base == 0 ? kHalf1 : 0;
+            nxt_cap = kHalfWords;
+            stage_span(nindex + g.nchunks, nxt, stage, nxt_base);
+            if (active) {
+              nstart = nindex[chunk];
+              nstop = chunk + 1 < g.nchunks ? nindex[chunk + 1] : (uint32_t)min<uint64_t>(words[i + 1], 0xFFFFFFFFull);
+              noff = aux[i + 1][blk];
+            }
+          }
+        }
+        if (active && ok) {
+          if (!cur.ok || words[i] > 0xFFFFFFFFull || start > stop || stop > words[i] ||
+              off >= (uint64_t)(stop - start) * 32 || start < cur.s0 || stop > cur.s1) {
+            ok = false;
+          } else {
+            const uint32_t s0 = (uint32_t)cur.s0;
+            LBits r;
+            r.init(stage + cur_base, start - s0 + (off >> 5), stop - s0, cur_cap);
+            r.skip((uint32_t)(off & 31));
+            ok = decode_block_codec<T, kCodec, decltype(route)::value>(r, minexp[i], step[i], acc, sq,
+                                                                        (relmask >> i) & 1u) && !r.bad();
+          }
+        }
+        if (i + 1 < ncomp && !pre) {  // staged after this component, into the whole buffer's first half or all of it
+          __syncthreads();  // every lane is done with this component's words
+          nxt_base = 0;
+          nxt_cap = nxt.s1 - nxt.s0 <= kHalfWords ? kHalfWords : kStageWords;
+          if (nxt.ok) stage_span(nindex + g.nchunks, nxt, stage, 0);
+          if (active) {
+            nstart = nindex[chunk];
+            nstop = chunk + 1 < g.nchunks ? nindex[chunk + 1] : (uint32_t)min<uint64_t>(words[i + 1], 0xFFFFFFFFull);
+            noff = aux[i + 1][blk];
+          }
+        }
+        cur = nxt;
+        cur_base = nxt_base;
+        cur_cap = nxt_cap;
+        start = nstart;
+        stop = nstop;
+        off = noff;
+    };
+    if constexpr (kHiRes) {
+      // the store's first component (if decoded here) on the full route,
+      // the residual ones on the high-half route only
+      int i = 0;
+      if (ncomp > 0 && !(relmask & 1u)) {
+        component(0, std::integral_constant<int, kRouteFull>{});
+        i = 1;
+      }
+      for (; i < ncomp; ++i) component(i, std::integral_constant<int, kRouteHi16>{});
+    } else {
+      for (int i = 0; i < ncomp; ++i) component(i, std::integral_constant<int, kRouteAuto>{});
+    }
+  } else {
+    for (int i = 0; i < ncomp; ++i) {
+      if (!active || !ok) continue;
+      const uint32_t* index = reinterpret_cast<const uint32_t*>(s[i] + kHeaderBytes);
+      const uint32_t* payload = index + g.nchunks;
+      const uint64_t start = index[chunk];
+      const uint64_t stop = chunk + 1 < g.nchunks ? (uint64_t)index[chunk + 1] : words[i];
+      const uint64_t off = aux[i][blk];
+      if (start > stop || stop > words[i] || stop > 0xFFFFFFFFull || off >= (stop - start) * 32) {
+        ok = false;
+        continue;
+      }
+      GBits r;
+      r.init(payload, (uint32_t)(start + (off >> 5)), (uint32_t)stop);
+      r.skip((uint32_t)(off & 31));
+      ok = decode_block_codec<T, kCodec>(r, minexp[i], step[i], acc, sq, (relmask >> i) & 1u) && !r.bad();
+    }
+  }
+  // a block whose stream did not parse is written as quiet NaNs, so the
+  // output never keeps stale memory (the status word reports it as well)
+  if (active && !ok) {
+#pragma unroll
+    for (int l = 0; l < 64; ++l) acc[l] = (T)__builtin_nan("");
+  }
+  // the block position is recomputed here rather than kept in registers
+  if (active) {
+    if constexpr (kBox) {
+      store_box(out, *box, block_pos(g, opaque(w) * 64 + lane), acc);
+    } else if constexpr (kFull) {
+      const BlockPos bo = block_pos(g, opaque(w) * 64 + lane);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) store_row(out, g, bo, r, acc + 4 * r, true);
+    } else {
+      store_block(out, g, block_pos(g, opaque(w) * 64 + lane), acc);
+    }
+  }
+  return ok || !active;
+}
+
+// kHiRes: the launch's residual components decode on the float32 high-half
+// route alone (the host has checked that every block of them qualifies)
+template <class T, bool kStaged, bool kFull, int kCodec, bool kHiRes = false>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 3 : 1))) void k_decode(DecArgs<T> a) {
+  __shared__ uint8_t s_squeeze[256];
+  __shared__ uint32_t s_stage[kStaged ? kStageWords + 3 : 1];
+  squeeze_table(s_squeeze);
+  if (!decode_wave<T, kStaged, false, kFull, kCodec, kHiRes>(a.g, a.s, a.aux, a.words, a.minexp, a.step, a.ncomp, a.relmask,
+                                                     a.in, a.out, blockIdx.x, s_squeeze, s_stage))
+    atomicOr(a.status, 1u);
+}
+
+// region retrieval: workgroup (row, i) decodes the i-th wave of the box's
+// block row `row` (rows in y-then-z order); waves past the row's last block
+// exit.  a.in / a.out are box arrays (a.in: the box after earlier components).
+// A wave whose blocks span several box rows (narrow fields) is staged once
+// per row, and each row's workgroup decodes only that row's blocks.
+template <class T, bool kStaged, int kCodec>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 3 : 1))) void k_decode_box(
+    DecArgs<T> a, BoxArgs b) {
+  __shared__ uint8_t s_squeeze[256];
+  __shared__ uint32_t s_stage[kStaged ? kStageWords + 3 : 1];
+  const uint32_t row = blockIdx.x / b.waves_per_row, i = blockIdx.x % b.waves_per_row;
+  const uint64_t nry = b.bhi[1] - b.blo[1];
+  const uint64_t by = b.blo[1] + row % nry, bz = b.blo[2] + row / nry;
+  b.row_first = (bz * a.g.nby + by) * a.g.nbx + b.blo[0];
+  b.row_last = (bz * a.g.nby + by) * a.g.nbx + b.bhi[0] - 1;
+  const uint64_t w = b.row_first / 64 + i;
+  if (w > b.row_last / 64) return;  // uniform over the workgroup
+  squeeze_table(s_squeeze);
+  if (!decode_wave<T, kStaged, true, false, kCodec>(a.g, a.s, a.aux, a.words, a.minexp, a.step, a.ncomp, a.relmask,
+                                                    a.in, a.out, w, s_squeeze, s_stage, &b))
+    atomicOr(a.status, 1u);
+}
+
+// many retrieval queries in one launch: wave w belongs to the query q with
+// wave_prefix[q] <= w < wave_prefix[q + 1]
+template <class T, bool kStaged, int kCodec, bool kHiRes = false>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 3 : 1))) void k_decode_queries(ServeArgs a) {
+  __shared__ uint8_t s_squeeze[256];
+  __shared__ uint32_t s_stage[kStaged ? kStageWords + 3 : 1];
+  squeeze_table(s_squeeze);
+  const uint32_t w = blockIdx.x;
+  uint32_t lo = 0, hi = a.nq;  // largest q with wave_prefix[q] <= w
+  while (hi - lo > 1) {
+    const uint32_t mid = (lo + hi) / 2;
+    if (a.wave_prefix[mid] <= w) lo = mid;
+    else hi = mid;
+  }
+  // the query table is read-only for the launch: read through the constant
+  // address space, so its values can be loaded again where needed instead of
+  // being held across the wave's work
+  typedef __attribute__((address_space(4))) const QueryDev CQueryDev;
+  const CQueryDev& q = ((const CQueryDev*)a.q)[lo];
+  Geo g;
+  g.nx = q.g.nx;
+  g.ny = q.g.ny;
+  g.nz = q.g.nz;
+  g.nbx = q.g.nbx;
+  g.nby = q.g.nby;
+  g.nbz = q.g.nbz;
+  g.nblocks = q.g.nblocks;
+  g.nchunks = q.g.nchunks;
+  g.rows_aligned = q.g.rows_aligned;
+  g.pad = 0;
+  if (!decode_wave<T, kStaged, false, false, kCodec, kHiRes>(
+          g, (const uint8_t* const*)q.s, (const uint32_t* const*)q.aux, (const uint64_t*)q.words,
+          (const int*)q.minexp, (const double*)q.step, q.ncomp, q.relmask, reinterpret_cast<const T*>(q.in),
+          reinterpret_cast<T*>(q.out), w - a.wave_prefix[lo], s_squeeze, s_stage))
+    atomicOr(a.status, 1u);
+}
+
+// ---------------------------------------------------------------------------
+// launchers
+template <class T, int kCodec>
+void launch_decode_codec(const DecArgs<T>& a, uint64_t max_span, bool hires, hipStream_t s) {
+  const uint64_t wgs = (a.g.nblocks + 63) / 64;
+  const dim3 grid((uint32_t)wgs), wg(64);
+  // every block full and every row aligned: the kernel without edge paths
+  const bool full = a.g.nx % 4 == 0 && a.g.ny % 4 == 0 && a.g.nz % 4 == 0 && a.g.rows_aligned;
+  if constexpr (sizeof(T) == 4 && kCodec == 0) {
+    if (hires && max_span <= kStageWords) {
+      if (full) hipLaunchKernelGGL((k_decode<T, true, true, kCodec, true>), grid, wg, 0, s, a);
+      else hipLaunchKernelGGL((k_decode<T, true, false, kCodec, true>), grid, wg, 0, s, a);
+      return;
+    }
+  }
+  if (max_span <= kStageWords) {
+    if (full) hipLaunchKernelGGL((k_decode<T, true, true, kCodec>), grid, wg, 0, s, a);
+    else hipLaunchKernelGGL((k_decode<T, true, false, kCodec>), grid, wg, 0, s, a);
+  } else {
+    if (full) hipLaunchKernelGGL((k_decode<T, false, true, kCodec>), grid, wg, 0, s, a);
+    else hipLaunchKernelGGL((k_decode<T, false, false, kCodec>), grid, wg, 0, s, a);
+  }
+}
+template <class T>
+hipError_t launch_decode(const DecArgs<T>& a, uint64_t max_span, int codec, bool hires, hipStream_t s) {
+  if (codec == 0) launch_decode_codec<T, 0>(a, max_span, hires, s);
+  else launch_decode_codec<T, 1>(a, max_span, false, s);
+  return hipGetLastError();
+}
+template <class T>
+hipError_t launch_decode_box(const DecArgs<T>& a, const BoxArgs& b, uint64_t max_span, int codec, hipStream_t s) {
+  const uint64_t rows = (b.bhi[1] - b.blo[1]) * (b.bhi[2] - b.blo[2]);
+  const uint64_t wgs = rows * b.waves_per_row;
+  if (wgs == 0) return hipSuccess;
+  const dim3 grid((uint32_t)wgs), wg(64);
+  const bool staged = max_span <= kStageWords;
+  if (codec == 0) {
+    if (staged) hipLaunchKernelGGL((k_decode_box<T, true, 0>), grid, wg, 0, s, a, b);
+    else hipLaunchKernelGGL((k_decode_box<T, false, 0>), grid, wg, 0, s, a, b);
+  } else {
+    if (staged) hipLaunchKernelGGL((k_decode_box<T, true, 1>), grid, wg, 0, s, a, b);
+    else hipLaunchKernelGGL((k_decode_box<T, false, 1>), grid, wg, 0, s, a, b);
+  }
+  return hipGetLastError();
+}
+template <class T>
+hipError_t launch_decode_queries(const ServeArgs& a, uint64_t max_span, int codec, bool hires, hipStream_t s) {
+  if (a.nwaves == 0) return hipSuccess;
+  const dim3 grid(a.nwaves), wg(64);
+  const bool staged = max_span <= kStageWords;
+  if constexpr (sizeof(T) == 4) {
+    if (codec == 0 && hires && staged) {
+      hipLaunchKernelGGL((k_decode_queries<T, true, 0, true>), grid, wg, 0, s, a);
+      return hipGetLastError();
+    }
+  }
+  if (codec == 0) {
+    if (staged) hipLaunchKernelGGL((k_decode_queries<T, true, 0>), grid, wg, 0, s, a);
+    else hipLaunchKernelGGL((k_decode_queries<T, false, 0>), grid, wg, 0, s, a);
+  } else {
+    if (staged) hipLaunchKernelGGL((k_decode_queries<T, true, 1>), grid, wg, 0, s, a);
+    else hipLaunchKernelGGL((k_decode_queries<T, false, 1>), grid, wg, 0, s, a);
+  }
+  return hipGetLastError();
+}
+
+}  // namespace pmc
