@@ -480,7 +480,8 @@ def main():
     nchunks = ((x.shape[2] + 3) // 4 * ((x.shape[1] + 3) // 4) * ((x.shape[0] + 3) // 4) + 15) // 16
     payload = [(m["bytes"] - 64 - 4 * nchunks) for m in info]
     # algorithmic bytes per step for each kernel
-    enc_bytes = sum(N * s * (1 + (i > 0) + (i < n - 1)) + payload[i] + 4 * nchunks for i in range(n))
+    # (one encoder launch takes every component: x is read once)
+    enc_bytes = N * s + sum(payload[i] + 4 * nchunks for i in range(n))
     if args.literal:
         dec_bytes = sum(sum(info[i]["bytes"] + (N * s if i > 0 else 0) + N * s for i in range(k))
                         for k in range(1, n + 1))

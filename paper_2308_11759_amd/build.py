@@ -17,7 +17,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpmc.so")
-SOURCES = ["kernels.hip", "decode_f32.hip", "decode_f64.hip", "capi.cpp", "batch.cpp", "server.cpp", "format.cpp"]
+SOURCES = ["kernels.hip", "encode_f32.hip", "encode_f64.hip", "decode_f32.hip",
+           "decode_f64.hip", "pack.hip", "capi.cpp", "batch.cpp", "server.cpp", "format.cpp"]
 ARCH = os.environ.get("PMC_OFFLOAD_ARCH", "gfx950")
 
 

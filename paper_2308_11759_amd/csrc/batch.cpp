@@ -1,8 +1,8 @@
 // batch.cpp -- many fields of uneven sizes and mixed types compressed together
 // (Alg. 1, Sec. 4.1, for every field).  All components of all fields run as
-// one captured HIP graph: per component, a persistent encode kernel per
-// element type over a list of (field, 64-block wave) items, a segmented chunk
-// scan and a batched pack.  The schedule (persistent grid size, item order)
+// one captured HIP graph: a persistent encode kernel per element type over a
+// list of (field, 64-block wave) items, each taken through every component,
+// then the scan and pack of every stream.  The schedule (persistent grid size, item order)
 // is picked by a small autotuner; every schedule yields identical bytes since
 // each wave's output depends only on its own blocks.
 #include <hip/hip_runtime.h>
@@ -30,15 +30,15 @@ struct pmc_batch {
   std::vector<std::vector<double>> tau;
   std::vector<std::vector<int>> minexp;
   // workspace layout (byte offsets into d_ws)
-  std::vector<uint64_t> off_xt0, off_xt1, off_staging, off_cw, off_offs, off_tiles, off_berr;
+  std::vector<uint64_t> off_job, job_bytes;
   std::vector<uint64_t> meta_first;  // index of the field's first CompMeta
   uint64_t off_table = 0, off_items = 0, off_meta = 0, ws_total = 0;
   // stream regions (byte offsets into d_streams)
   std::vector<uint64_t> region_off, region_cap;
   uint64_t streams_total = 0;
-  // items: [encode f32 | encode f64 | scan tiles | chunk quads]
+  // items: [encode f32 | encode f64 | pack tiles]
   std::vector<Item> items;
-  uint32_t n32 = 0, n64 = 0, ntiles = 0, nquads = 0;
+  uint32_t n32 = 0, n64 = 0, ntiles = 0;
   uint64_t items_cap = 0;
   // schedule
   int grid_mult = 4, order = 0;
@@ -82,15 +82,9 @@ void build_items(pmc_batch* b) {
   }
   b->ntiles = 0;
   for (int i = 0; i < b->nf; ++i) {
-    const uint64_t t = (b->g[i].nchunks + kScanTile - 1) / kScanTile;
+    const uint64_t t = (b->g[i].nchunks + kPackTile - 1) / kPackTile;
     for (uint64_t j = 0; j < t; ++j) b->items.push_back(Item{(uint32_t)i, (uint32_t)j});
     b->ntiles += (uint32_t)t;
-  }
-  b->nquads = 0;
-  for (int i = 0; i < b->nf; ++i) {
-    const uint64_t q = (b->g[i].nchunks + 3) / 4;
-    for (uint64_t j = 0; j < q; ++j) b->items.push_back(Item{(uint32_t)i, (uint32_t)j});
-    b->nquads += (uint32_t)q;
   }
 }
 
@@ -167,7 +161,7 @@ pmc_status pmc_batch_plan(pmc_ctx* ctx, int nf, const pmc_field* fields, const i
   hipDeviceProp_t prop;
   if (hipGetDeviceProperties(&prop, ctx->device) == hipSuccess && prop.multiProcessorCount > 0)
     b->cus = prop.multiProcessorCount;
-  uint64_t ws = 0, nmeta = 0, reg = 0;
+  uint64_t ws = 0, nmeta = 0, reg = 0, room = 0;
   for (int i = 0; i < nf; ++i) {
     Geo g;
     if (!make_geo(&fields[i], &g) || n[i] < 1 || n[i] > kMaxComps || !tau[i]) {
@@ -189,23 +183,11 @@ pmc_status pmc_batch_plan(pmc_ctx* ctx, int nf, const pmc_field* fields, const i
     b->tau.push_back(t);
     b->minexp.push_back(me);
     b->maxn = std::max(b->maxn, n[i]);
-    // x~ ping-pong buffers (component i reads buffer (i-1)&1, writes i&1),
-    // in the encoder's tiled layout: 64 * 64 values per wave of 64 blocks
-    const uint64_t tile = align256((g.nblocks + 63) / 64 * 4096 * elem_size(&fields[i]));
-    b->off_xt0.push_back(ws);
-    if (n[i] > 1) ws += tile;
-    b->off_xt1.push_back(ws);
-    if (n[i] > 2) ws += tile;
-    b->off_staging.push_back(ws);
-    ws += align256(g.nchunks * chunk_cap_words_host(fields[i].dtype) * 4);
-    b->off_cw.push_back(ws);
-    ws += align256(g.nchunks * 4);
-    b->off_offs.push_back(ws);
-    ws += align256(g.nchunks * 4);
-    b->off_tiles.push_back(ws);
-    ws += align256((g.nchunks + kScanTile - 1) / kScanTile * 8);
-    b->off_berr.push_back(ws);  // per-block error carried between components
-    if (n[i] > 1) ws += align256(g.nblocks * 8);
+    b->off_job.push_back(ws);
+    b->job_bytes.push_back(job_workspace(&fields[i], g, n[i]));
+    ws += b->job_bytes.back();
+    // (the items' room: this many per field beside the encoder's waves)
+    room += (g.nblocks + 63) / 64 + (g.nchunks + 1023) / 1024 + (g.nchunks + 3) / 4;
     b->meta_first.push_back(nmeta);
     nmeta += n[i];
     b->region_off.push_back(reg);
@@ -214,7 +196,7 @@ pmc_status pmc_batch_plan(pmc_ctx* ctx, int nf, const pmc_field* fields, const i
     reg += align256(cap);
   }
   b->off_table = ws;
-  ws += align256((uint64_t)nf * sizeof(FieldDev));
+  ws += align256((uint64_t)nf * sizeof(FieldJob));
   b->off_meta = ws;
   ws += align256(nmeta * sizeof(CompMeta));
   b->off_items = ws;
@@ -224,7 +206,7 @@ pmc_status pmc_batch_plan(pmc_ctx* ctx, int nf, const pmc_field* fields, const i
     b->order = od;
   }
   build_items(b);
-  b->items_cap = b->items.size();
+  b->items_cap = room;  // at least items.size(): a pack tile takes the place of 64 chunk quads
   ws += align256(b->items_cap * sizeof(Item));
   b->ws_total = ws;
   b->streams_total = reg;
@@ -261,29 +243,29 @@ pmc_status pmc_batch_get_schedule(const pmc_batch* b, int* grid_mult, int* order
   return PMC_OK;
 }
 
+// the encoder of each element type, then the pack of every stream
+static hipError_t batch_kernels(pmc_batch* b, const uint8_t* ws, int comps, hipStream_t stream) {
+  const FieldJob* table = (const FieldJob*)(ws + b->off_table);
+  const Item* items = (const Item*)(ws + b->off_items);
+  const uint32_t grid = (uint32_t)(b->grid_mult * b->cus);
+  hipError_t e = hipSuccess;
+  BatchArgs a{table, (uint32_t)b->nf, items, b->n32};
+  if (b->n32) e = launch_encode_batch<float>(a, std::min<uint32_t>(grid, b->n32), stream);
+  a.items = items + b->n32;
+  a.nitems = b->n64;
+  if (e == hipSuccess && b->n64) e = launch_encode_batch<double>(a, std::min<uint32_t>(grid, b->n64), stream);
+  a.items = items + b->n32 + b->n64;
+  a.nitems = b->ntiles;
+  if (e == hipSuccess) e = launch_batch_pack(a, (uint32_t)comps, stream);
+  return e;
+}
+
 static pmc_status batch_capture(pmc_batch* b, uint8_t* ws, uint8_t* streams) {
   pmc_ctx* ctx = b->ctx;
   drop_graph(b);
-  const FieldDev* table = (const FieldDev*)(ws + b->off_table);
-  const Item* items = (const Item*)(ws + b->off_items);
   hipError_t e = hipStreamBeginCapture(b->cap_stream, hipStreamCaptureModeThreadLocal);
   if (e != hipSuccess) return hipfail(ctx, e, "begin capture");
-  hipError_t le = launch_batch_init(table, (uint32_t)b->nf, b->cap_stream);
-  const uint32_t grid = (uint32_t)(b->grid_mult * b->cus);
-  for (int c = 0; c < b->maxn && le == hipSuccess; ++c) {
-    BatchArgs a{table, (uint32_t)b->nf, items, b->n32, c};
-    if (b->n32) le = launch_encode_batch<float>(a, std::min<uint32_t>(grid, b->n32), b->cap_stream);
-    a.items = items + b->n32;
-    a.nitems = b->n64;
-    if (le == hipSuccess && b->n64)
-      le = launch_encode_batch<double>(a, std::min<uint32_t>(grid, b->n64), b->cap_stream);
-    a.items = items + b->n32 + b->n64;
-    a.nitems = b->ntiles;
-    if (le == hipSuccess) le = launch_batch_scan(a, (uint32_t)b->nf, b->cap_stream);
-    a.items = items + b->n32 + b->n64 + b->ntiles;
-    a.nitems = b->nquads;
-    if (le == hipSuccess) le = launch_batch_pack(a, b->cap_stream);
-  }
+  const hipError_t le = batch_kernels(b, ws, b->maxn, b->cap_stream);
   e = hipStreamEndCapture(b->cap_stream, &b->graph);
   if (le != hipSuccess) return hipfail(ctx, le, "capture launch");
   if (e != hipSuccess) return hipfail(ctx, e, "end capture");
@@ -296,36 +278,30 @@ static pmc_status batch_capture(pmc_batch* b, uint8_t* ws, uint8_t* streams) {
   return PMC_OK;
 }
 
-// upload the field table (current input pointers) and items, then replay
-static pmc_status batch_launch(pmc_batch* b, const void* const* d_x, uint8_t* ws, uint8_t* streams) {
+// upload the job table (current input pointers) for components [c0, c1) of
+// every field, and the items if they are not there; waits for the copies
+static pmc_status batch_upload(pmc_batch* b, const void* const* d_x, uint8_t* ws, uint8_t* streams, int c0, int c1) {
   pmc_ctx* ctx = b->ctx;
-  std::vector<FieldDev> tab(b->nf);
+  std::vector<FieldJob> tab(b->nf);
   for (int i = 0; i < b->nf; ++i) {
-    FieldDev& d = tab[i];
+    FieldJob& d = tab[i];
     std::memset(&d, 0, sizeof(d));
+    if (!job_layout(&b->f[i], b->g[i], b->n[i], b->n[i] > 1 && (c0 > 0 || c1 < b->maxn), ws + b->off_job[i],
+                    b->job_bytes[i], &d))
+      return fail(ctx, PMC_E_NOMEM, "field %d: workspace too small for its layout", i);
     d.x = d_x[i];
-    d.xt[0] = ws + b->off_xt0[i];
-    d.xt[1] = ws + b->off_xt1[i];
-    d.g = b->g[i];
-    d.staging = (uint32_t*)(ws + b->off_staging[i]);
-    d.chunk_words = (uint32_t*)(ws + b->off_cw[i]);
-    d.offsets = (uint32_t*)(ws + b->off_offs[i]);
-    d.tile_sums = (unsigned long long*)(ws + b->off_tiles[i]);
-    d.berr = (double*)(ws + b->off_berr[i]);
+    d.comp0 = (uint8_t)std::min(c0, b->n[i]);
+    d.comp1 = (uint8_t)std::min(c1, b->n[i]);
     d.region = streams + b->region_off[i];
-    d.aux0 = (uint32_t*)d.region;
     d.aux_stride = aux_bytes(b->g[i]) / 4;
-    d.meta0 = (CompMeta*)(ws + b->off_meta) + b->meta_first[i];
+    d.meta = (CompMeta*)(ws + b->off_meta) + b->meta_first[i];
     d.region_cap = b->region_cap[i];
-    d.ncomp = b->n[i];
-    d.dtype = b->f[i].dtype;
-    d.ntiles = (uint32_t)((b->g[i].nchunks + kScanTile - 1) / kScanTile);
     for (int c = 0; c < b->n[i]; ++c) {
       d.tau[c] = b->tau[i][c];
       d.minexp[c] = b->minexp[i][c];
     }
   }
-  hipError_t e = hipMemcpyAsync(ws + b->off_table, tab.data(), tab.size() * sizeof(FieldDev),
+  hipError_t e = hipMemcpyAsync(ws + b->off_table, tab.data(), tab.size() * sizeof(FieldJob),
                                 hipMemcpyHostToDevice, ctx->stream);
   if (e == hipSuccess && !b->items_uploaded) {
     e = hipMemcpyAsync(ws + b->off_items, b->items.data(), b->items.size() * sizeof(Item), hipMemcpyHostToDevice,
@@ -335,10 +311,19 @@ static pmc_status batch_launch(pmc_batch* b, const void* const* d_x, uint8_t* ws
   // the host vectors above are pageable: wait for the copies before they go
   if ((e = hipStreamSynchronize(ctx->stream)) != hipSuccess) return hipfail(ctx, e, "sync");
   b->items_uploaded = true;
+  return PMC_OK;
+}
+
+// upload, then replay the graph (captured again when buffers or schedule changed)
+static pmc_status batch_launch(pmc_batch* b, const void* const* d_x, uint8_t* ws, uint8_t* streams) {
+  pmc_ctx* ctx = b->ctx;
+  pmc_status st = batch_upload(b, d_x, ws, streams, 0, b->maxn);
+  if (st != PMC_OK) return st;
   if (!b->exec || b->g_ws != ws || b->g_streams != streams || b->g_grid != b->grid_mult || b->g_order != b->order) {
-    pmc_status st = batch_capture(b, ws, streams);
+    st = batch_capture(b, ws, streams);
     if (st != PMC_OK) return st;
   }
+  hipError_t e;
   {
     ProfScope ps(ctx, "batch_graph");
     e = hipGraphLaunch(b->exec, ctx->stream);
@@ -369,14 +354,29 @@ pmc_status pmc_batch_compress(pmc_batch* b, const void* const* d_x, void* d_ws, 
   if (st != PMC_OK) return st;
   const uint64_t nmeta = b->meta_first.back() + b->n.back();
   std::vector<CompMeta> hm(nmeta);
-  e = hipMemcpyAsync(hm.data(), ws + b->off_meta, nmeta * sizeof(CompMeta), hipMemcpyDeviceToHost, ctx->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-  if (e != hipSuccess) return hipfail(ctx, e, "meta copy");
   unsigned int flags = 0;
   unsigned long long misses = 0;
-  for (const CompMeta& m : hm) {
-    flags |= m.flags;
-    misses += m.nmiss;
+  auto results = [&]() {
+    hipError_t r = hipMemcpyAsync(hm.data(), ws + b->off_meta, nmeta * sizeof(CompMeta), hipMemcpyDeviceToHost,
+                                  ctx->stream);
+    if (r == hipSuccess) r = hipStreamSynchronize(ctx->stream);
+    flags = 0;
+    misses = 0;
+    for (const CompMeta& m : hm) {
+      flags |= m.flags;
+      misses += m.nmiss;
+    }
+    return r;
+  };
+  if ((e = results()) != hipSuccess) return hipfail(ctx, e, "meta copy");
+  if ((flags & FLAG_STAGING) && !(flags & FLAG_NONFINITE)) {
+    // the components of some wave did not fit its slot together: one round
+    // of launches per component
+    for (int c = 0; c < b->maxn; ++c) {
+      if ((st = batch_upload(b, d_x, ws, streams, c, c + 1)) != PMC_OK) return st;
+      if ((e = batch_kernels(b, ws, 1, ctx->stream)) != hipSuccess) return hipfail(ctx, e, "encode");
+    }
+    if ((e = results()) != hipSuccess) return hipfail(ctx, e, "meta copy");
   }
   if (flags & FLAG_NONFINITE) return fail(ctx, PMC_E_NONFINITE, "input holds NaN or Inf");
   if (flags & (FLAG_INDEX | FLAG_OVERFLOW)) return fail(ctx, PMC_E_NOMEM, "a stream exceeds its capacity");

@@ -103,6 +103,7 @@ __device__ __forceinline__ void load_block(const T* __restrict__ f, const Geo& g
 // only push out lines this launch still reads
 typedef float nt_f4 __attribute__((ext_vector_type(4)));
 typedef double nt_d2 __attribute__((ext_vector_type(2)));
+typedef uint32_t nt_u4 __attribute__((ext_vector_type(4)));
 template <class T>
 __device__ __forceinline__ void store_row16_nt(T* row, T a, T b, T c, T d) {
   if constexpr (sizeof(T) == 4) {

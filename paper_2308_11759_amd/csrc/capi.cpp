@@ -39,35 +39,56 @@ pmc_status hipfail(pmc_ctx* ctx, hipError_t e, const char* what) {
 
 uint64_t elem_size(const pmc_field* f) { return f->dtype == PMC_F32 ? 4 : 8; }
 
-struct WsLayout {
-  uint64_t xt[2], staging, chunk_words, offsets, tile_sums, meta, berr, total;
-};
-
-// x~ is double-buffered: component i reads x~_{i-1} from xt[(i-1) & 1] and
-// writes x~_i to xt[i & 1] (the first reads nothing, the last writes nothing),
-// each in the encoder's tiled layout: 64 * 64 values per wave of 64 blocks
-WsLayout ws_layout(const pmc_field* f, const Geo& g, int n) {
-  WsLayout w{};
-  uint64_t o = 0;
-  const uint64_t field = align256((g.nblocks + 63) / 64 * 4096 * elem_size(f));
-  w.xt[0] = o;
-  if (n > 1) o += field;
-  w.xt[1] = o;
-  if (n > 2) o += field;
-  w.staging = o;
-  o += align256(g.nchunks * chunk_cap_words_host(f->dtype) * 4);
-  w.chunk_words = o;
-  o += align256(g.nchunks * 4);
-  w.offsets = o;
-  o += align256(g.nchunks * 4);
-  w.tile_sums = o;
-  o += align256((g.nchunks + kScanTile - 1) / kScanTile * 8);
-  w.meta = o;
-  o += align256((uint64_t)n * sizeof(CompMeta));
-  w.berr = o;  // per-block error carried from one component to the next
+uint64_t job_workspace(const pmc_field* f, const Geo& g, int n) {
+  const uint64_t tiles = align256((g.nblocks + 63) / 64 * 4096 * elem_size(f));
+  uint64_t o = align256(g.nchunks * chunk_cap_words_host(f->dtype) * 4);  // one component, every block raw
+  if (n > 1) o += tiles;
+  if (n > 2) o += tiles;
+  o += 2 * align256(g.nchunks * 4) + align256((g.nchunks + 1023) / 1024 * 8);
   if (n > 1) o += align256(g.nblocks * 8);
-  w.total = o;
-  return w;
+  return o;
+}
+
+// The workspace of one field: the staging slots, and at its end the records.
+// A slot holds every component's span of its wave one behind the other: n
+// components with every block raw for n <= 2, 96 bits per float32 and 192 per
+// float64 value for more.  Data that needs more has its components run one
+// launch each (FLAG_STAGING; apart): a slot then holds one component with
+// every block raw, and x~ between the launches takes a tile per wave in front.
+bool job_layout(const pmc_field* f, const Geo& g, int n, bool apart, uint8_t* ws, uint64_t bytes, FieldJob* job) {
+  const uint64_t nwaves = (g.nblocks + 63) / 64, ntiles = (g.nchunks + kPackTile - 1) / kPackTile;
+  const uint64_t one = 4 * chunk_cap_words_host(f->dtype);  // words of a wave with every block raw
+  if (nwaves > 0xFFFFFFFFull) return false;
+  uint64_t end = bytes & ~15ull;
+  auto take = [&](uint64_t size) {  // an array at the end of what is left
+    size = (size + 15) & ~15ull;
+    if (end < size) return (uint8_t*)nullptr;
+    end -= size;
+    return ws + end;
+  };
+  job->chunk_words = (uint32_t*)take((uint64_t)n * g.nchunks * 4);
+  job->wave_linf = (double*)take((uint64_t)n * nwaves * 8);
+  job->wave_stat = (uint32_t*)take((uint64_t)n * nwaves * 4);
+  job->wave_start = n > 1 ? (uint32_t*)take((uint64_t)n * nwaves * 4) : nullptr;
+  job->tile_recs = (TileRec*)take((uint64_t)n * ntiles * sizeof(TileRec));
+  const uint64_t tiles = apart ? align256(nwaves * 4096 * elem_size(f)) : 0;
+  if (!job->tile_recs || end < tiles) return false;
+  const uint64_t words = (end - tiles) / 16 * 4;
+  const uint64_t slot = apart || n <= 2 ? one * (apart ? 1 : n) : std::min<uint64_t>(words / nwaves / 4 * 4, 0x40000000ull);
+  if (words < (nwaves - 1) * slot) return false;
+  const uint64_t last = std::min(slot, (words - (nwaves - 1) * slot) / 4 * 4);
+  const uint64_t need = ((g.nchunks - 4 * (nwaves - 1)) * chunk_cap_words_host(f->dtype) + 3) / 4 * 4;
+  if (last < need || (nwaves > 1 && slot < one)) return false;
+  job->tiles = ws;
+  job->staging = (uint32_t*)(ws + tiles);
+  job->slot_words = (uint32_t)slot;
+  job->slot_last = (uint32_t)last;
+  job->g = g;
+  job->ncomp = (uint8_t)n;
+  job->comp0 = 0;
+  job->comp1 = (uint8_t)n;
+  job->dtype = (uint8_t)f->dtype;
+  return true;
 }
 
 uint64_t stream_cap_one(const Geo& g, int dtype) {
@@ -102,6 +123,11 @@ pmc_store* store_from_meta(const pmc_field* f, const Geo& g, int n, const double
     s->full.push_back(hm[i].full);
   }
   return s;
+}
+
+// pmc_compress's workspace: one field's, and its components' results
+static uint64_t single_workspace(const pmc_field* f, const Geo& g, int n) {
+  return job_workspace(f, g, n) + align256((uint64_t)n * sizeof(CompMeta));
 }
 
 }  // namespace pmc_host
@@ -379,8 +405,7 @@ pmc_status pmc_cast_retrieve(pmc_ctx* ctx, const pmc_field* f, const float* d_co
 pmc_status pmc_compress_sizes(const pmc_field* f, int n, size_t* ws_bytes, size_t* stream_cap_per_comp) {
   Geo g;
   if (!make_geo(f, &g) || n < 1 || n > kMaxComps) return PMC_E_ARG;
-  WsLayout w = ws_layout(f, g, n);
-  if (ws_bytes) *ws_bytes = w.total;
+  if (ws_bytes) *ws_bytes = single_workspace(f, g, n);
   if (stream_cap_per_comp) *stream_cap_per_comp = aux_bytes(g) + align256(stream_cap_one(g, f->dtype));
   return PMC_OK;
 }
@@ -402,9 +427,9 @@ pmc_status pmc_compress(pmc_ctx* ctx, const pmc_field* f, const void* d_x, int n
     if (codec == 1 && !(tau[i] >= std::ldexp(1.0, -960) && tau[i] <= std::ldexp(1.0, 1000)))
       return fail(ctx, PMC_E_ARG, "tau[%d] outside [2^-960, 2^1000], the prediction codec's range", i);
   }
-  WsLayout w = ws_layout(f, g, n);
-  if (!d_ws || ws_bytes < w.total)
-    return fail(ctx, PMC_E_NOMEM, "workspace too small: need %llu bytes", (unsigned long long)w.total);
+  const uint64_t ws_need = single_workspace(f, g, n);
+  if (!d_ws || ws_bytes < ws_need)
+    return fail(ctx, PMC_E_NOMEM, "workspace too small: need %llu bytes", (unsigned long long)ws_need);
   // the per-block indexes sit at the front of d_streams and are written by
   // the encoder directly; the streams themselves are capacity-checked on the
   // device before they are packed
@@ -414,108 +439,65 @@ pmc_status pmc_compress(pmc_ctx* ctx, const pmc_field* f, const void* d_x, int n
                 (unsigned long long)min_cap);
   hipError_t e = hipSetDevice(ctx->device);
   if (e != hipSuccess) return hipfail(ctx, e, "hipSetDevice");
-  uint8_t* ws = (uint8_t*)d_ws;
-  CompMeta* meta = (CompMeta*)(ws + w.meta);
-  // every counter zero; component 0's stream starts after the n block indexes
   const uint64_t auxb = aux_bytes(g);
-  if ((e = launch_fill64_one((unsigned long long*)meta, (uint64_t)n * sizeof(CompMeta) / 8, 0ull,
-                             offsetof(CompMeta, stream_offset) / 8, (unsigned long long)(n * auxb), ctx->stream)) !=
-      hipSuccess)
-    return hipfail(ctx, e, "meta init");
-
+  FieldJob job{};
+  const uint64_t meta_bytes = align256((uint64_t)n * sizeof(CompMeta));
+  if (!job_layout(f, g, n, false, (uint8_t*)d_ws, ws_need - meta_bytes, &job))
+    return fail(ctx, PMC_E_NOMEM, "workspace too small for its layout");
+  job.meta = (CompMeta*)((uint8_t*)d_ws + ws_need - meta_bytes);
+  job.x = d_x;
+  job.region = (uint8_t*)d_streams;
+  job.region_cap = streams_cap;
+  job.aux_stride = auxb / 4;
+  job.codec = (uint8_t)codec;
   std::vector<int> minexp(n);
   for (int i = 0; i < n; ++i) {
     minexp[i] = floor_log2(tau[i]);
-    ScanArgs sa{};
-    sa.chunk_words = (const uint32_t*)(ws + w.chunk_words);
-    sa.offsets = (uint32_t*)(ws + w.offsets);
-    sa.tile_sums = (unsigned long long*)(ws + w.tile_sums);
-    sa.aux_bytes = auxb;
-    sa.nchunks = g.nchunks;
-    sa.meta = meta;
-    sa.comp = i;
-    sa.ncomp = n;
-    sa.streams_cap = streams_cap;
-    PackArgs pa{};
-    pa.staging = (const uint32_t*)(ws + w.staging);
-    pa.chunk_words = sa.chunk_words;
-    pa.offsets = sa.offsets;
-    pa.nchunks = g.nchunks;
-    pa.meta = meta;
-    pa.comp = i;
-    pa.minexp = minexp[i];
-    pa.streams = (uint8_t*)d_streams;
-    pa.g = g;
-    pa.tau = tau[i];
-    pa.codec = codec;
-    if (f->dtype == PMC_F32) {
-      EncArgs<float> a{};
-      a.x = (const float*)d_x;
-      a.xt_in = i > 0 ? (const float*)(ws + w.xt[(i - 1) & 1]) : nullptr;
-      a.xt_out = (float*)(ws + w.xt[i & 1]);
-      a.g = g;
-      a.tau = tau[i];
-      a.minexp = minexp[i];
-      a.first = i == 0;
-      a.last = i == n - 1;
-      a.staging = (uint32_t*)(ws + w.staging);
-      a.chunk_words = (uint32_t*)(ws + w.chunk_words);
-      a.aux = (uint32_t*)((uint8_t*)d_streams + i * auxb);
-      a.meta = meta + i;
-      a.berr = (double*)(ws + w.berr);
-      a.h0 = 2.0 * tau[i];
-      a.inv0 = 1.0 / a.h0;
-      {
-        ProfScope ps(ctx, codec == 0 ? "k_encode_f32" : "k_encode_pq_f32");
-        e = launch_encode<float>(a, codec, ctx->stream);
-      }
-      if (e != hipSuccess) return hipfail(ctx, e, "encode");
-      {
-        ProfScope ps(ctx, "k_scan");
-        e = launch_scan(sa, ctx->stream);
-      }
-      if (e != hipSuccess) return hipfail(ctx, e, "scan");
-      {
-        ProfScope ps(ctx, "k_pack_f32");
-        e = launch_pack<float>(pa, ctx->stream);
-      }
-      if (e != hipSuccess) return hipfail(ctx, e, "pack");
-    } else {
-      EncArgs<double> a{};
-      a.x = (const double*)d_x;
-      a.xt_in = i > 0 ? (const double*)(ws + w.xt[(i - 1) & 1]) : nullptr;
-      a.xt_out = (double*)(ws + w.xt[i & 1]);
-      a.g = g;
-      a.tau = tau[i];
-      a.minexp = minexp[i];
-      a.first = i == 0;
-      a.last = i == n - 1;
-      a.staging = (uint32_t*)(ws + w.staging);
-      a.chunk_words = (uint32_t*)(ws + w.chunk_words);
-      a.aux = (uint32_t*)((uint8_t*)d_streams + i * auxb);
-      a.meta = meta + i;
-      a.berr = (double*)(ws + w.berr);
-      a.h0 = 2.0 * tau[i];
-      a.inv0 = 1.0 / a.h0;
-      {
-        ProfScope ps(ctx, codec == 0 ? "k_encode_f64" : "k_encode_pq_f64");
-        e = launch_encode<double>(a, codec, ctx->stream);
-      }
-      if (e != hipSuccess) return hipfail(ctx, e, "encode");
-      {
-        ProfScope ps(ctx, "k_scan");
-        e = launch_scan(sa, ctx->stream);
-      }
-      if (e != hipSuccess) return hipfail(ctx, e, "scan");
-      {
-        ProfScope ps(ctx, "k_pack_f64");
-        e = launch_pack<double>(pa, ctx->stream);
-      }
-      if (e != hipSuccess) return hipfail(ctx, e, "pack");
-    }
+    job.tau[i] = tau[i];
+    job.minexp[i] = minexp[i];
   }
+  // the per-component results also go straight to the pinned buffer
+  void* dev_pin = nullptr;
+  if (!ctx->pin || hipHostGetDevicePointer(&dev_pin, ctx->pin, 0) != hipSuccess) dev_pin = nullptr;
+  job.host_meta = (CompMeta*)dev_pin;
   std::vector<CompMeta> hm(n);
-  if ((e = read_back(ctx, hm.data(), meta, n * sizeof(CompMeta))) != hipSuccess) return hipfail(ctx, e, "meta read");
+  // components [c0, c1) in one launch of the encoder and one of each pack kernel
+  auto run = [&](int c0, int c1) {
+    job.comp0 = (uint8_t)c0;
+    job.comp1 = (uint8_t)c1;
+    hipError_t r;
+    {
+      ProfScope ps(ctx, f->dtype == PMC_F32 ? (codec == 0 ? "k_encode_f32" : "k_encode_pq_f32")
+                                            : (codec == 0 ? "k_encode_f64" : "k_encode_pq_f64"));
+      r = f->dtype == PMC_F32 ? launch_encode<float>(job, ctx->stream) : launch_encode<double>(job, ctx->stream);
+    }
+    if (r != hipSuccess) return r;
+    ProfScope ps(ctx, f->dtype == PMC_F32 ? "k_pack_f32" : "k_pack_f64");
+    return launch_pack(job, ctx->stream);
+  };
+  auto results = [&]() {
+    hipError_t r;
+    if (!dev_pin) return read_back(ctx, hm.data(), job.meta, n * sizeof(CompMeta));
+    if ((r = hipStreamSynchronize(ctx->stream)) != hipSuccess) return r;
+    std::memcpy(hm.data(), ctx->pin, n * sizeof(CompMeta));
+    return hipSuccess;
+  };
+  if ((e = run(0, n)) != hipSuccess) return hipfail(ctx, e, "encode");
+  if ((e = results()) != hipSuccess) return hipfail(ctx, e, "meta read");
+  bool over = false, nonfinite = false;
+  for (int i = 0; i < n; ++i) {
+    over = over || (hm[i].flags & FLAG_STAGING);
+    nonfinite = nonfinite || (hm[i].flags & FLAG_NONFINITE);
+  }
+  if (over && !nonfinite) {
+    // some wave's components did not fit its slot together: one launch per
+    // component
+    if (!job_layout(f, g, n, true, (uint8_t*)d_ws, ws_need - meta_bytes, &job))
+      return fail(ctx, PMC_E_NOMEM, "workspace too small for its layout");
+    for (int i = 0; i < n; ++i)
+      if ((e = run(i, i + 1)) != hipSuccess) return hipfail(ctx, e, "encode");
+    if ((e = results()) != hipSuccess) return hipfail(ctx, e, "meta read");
+  }
 
   unsigned int flags = 0;
   unsigned long long misses = 0;
@@ -543,7 +525,7 @@ pmc_status pmc_compress_static(pmc_ctx* ctx, const pmc_field* f, const void* d_x
   Geo g;
   if (!make_geo(f, &g)) return fail(ctx, PMC_E_ARG, "bad field");
   if (n < 1 || n > kMaxComps) return fail(ctx, PMC_E_ARG, "n must be in [1, %d]", kMaxComps);
-  const uint64_t need = ws_layout(f, g, n).total;
+  const uint64_t need = single_workspace(f, g, n);
   if (need > PMC_STATIC_WS_BYTES)
     return fail(ctx, PMC_E_NOMEM,
                 "field needs %llu bytes of workspace; the static workspace holds %llu (use pmc_compress "

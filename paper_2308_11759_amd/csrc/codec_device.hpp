@@ -2,9 +2,9 @@
 // codec for CDNA4 (gfx950).  One lane owns one 4x4x4 block: the 64 values, the
 // quantised integers and the negabinary coefficients all live in registers
 // (fully unrolled loops with compile-time indices), so the coefficient
-// reordering is free register renaming.  Bit planes are produced 16 at a time
-// by an in-register 32x32 bit-matrix transpose instead of 64 bit extractions
-// per plane.
+// reordering is free register renaming.  Bit planes are produced 4 or 8 at a
+// time, and taken apart 4, 8 or 16 at a time, by in-register bit-matrix
+// transposes instead of 64 bit extractions per plane.
 //
 // The codec realises, for d = 3, the compressor the paper plugs into its
 // multi-component loop (Sec. 4, Alg. 1 and Alg. 2): one common exponent per
@@ -155,118 +155,6 @@ template <class S> __device__ __forceinline__ void xform_fwd(S q[64]) {
 }
 
 // ---------------------------------------------------------------------------
-// 32x32 bit-matrix transpose in registers: afterwards A[r] bit c equals the
-// old A[c] bit r.  Recursive block swap with strides 16, 8, 4, 2, 1.
-// one butterfly stage: for each pair (a, b) = (A[k], A[k+J]) with bit J of k
-// clear, b takes the M-bits of a >> J and a the (M << J)-bits of b << J.
-// The 16- and 8-bit stages move whole bytes (one v_perm each); the others
-// exchange the masked bits through one xor-difference.
-template <int J, uint32_t M> __device__ __forceinline__ void tstage(uint32_t A[32]) {
-#pragma unroll
-  for (int k = 0; k < 32; ++k) {
-    if (k & J) continue;
-    const uint32_t a = A[k], b = A[k + J];
-    if constexpr (J == 16) {
-      A[k] = __builtin_amdgcn_perm(b, a, 0x05040100u);      // a.lo16 | b.lo16 << 16
-      A[k + J] = __builtin_amdgcn_perm(b, a, 0x07060302u);  // a.hi16 | b.hi16 << 16
-    } else if constexpr (J == 8) {
-      A[k] = __builtin_amdgcn_perm(b, a, 0x06020400u);      // a0 b0 a2 b2
-      A[k + J] = __builtin_amdgcn_perm(b, a, 0x07030501u);  // a1 b1 a3 b3
-    } else {
-      const uint32_t t = ((a >> J) ^ b) & M;
-      A[k + J] = b ^ t;
-      A[k] = a ^ (t << J);
-    }
-  }
-}
-__device__ __forceinline__ void transpose32(uint32_t A[32]) {
-  tstage<16, 0x0000FFFFu>(A);
-  tstage<8, 0x00FF00FFu>(A);
-  tstage<4, 0x0F0F0F0Fu>(A);
-  tstage<2, 0x33333333u>(A);
-  tstage<1, 0x55555555u>(A);
-}
-
-// 16 bits [base, base+16) of coefficients j and j+32 packed as one word
-__device__ __forceinline__ uint32_t slice16(uint32_t v, int base) { return (v >> base) & 0xFFFFu; }
-__device__ __forceinline__ uint32_t slice16(uint64_t v, int base) {
-  return (uint32_t)(v >> base) & 0xFFFFu;
-}
-
-// planes [base, base+16) of the 64 coefficients as 32 words T:
-//   plane base+r has coefficients 0..31 in T[r] and 32..63 in T[16+r]
-template <class U> __device__ __forceinline__ void plane_group(const U u[64], int base, uint32_t T[32]) {
-#pragma unroll
-  for (int j = 0; j < 32; ++j) T[j] = slice16(u[j], base) | (slice16(u[j + 32], base) << 16);
-  transpose32(T);
-}
-
-// bits one plane costs with the group-testing coder, given the significant
-// prefix n (updated); closed form of the coder's emissions
-__device__ __forceinline__ uint32_t plane_cost(uint64_t wd, uint32_t& n) {
-  uint32_t c = n;
-  if (n < 64) {
-    uint64_t rest = wd >> n;
-    if (rest == 0) {
-      c += 1;
-    } else {
-      uint32_t m = (uint32_t)__popcll(rest);
-      uint32_t h = 63u - (uint32_t)__clzll(rest) + n;
-      c += m + (h - n + 1) + (h < 63 ? 1u : 0u) - (h == 63 ? 1u : 0u);
-      n = h + 1;
-    }
-  }
-  return c;
-}
-
-// ---------------------------------------------------------------------------
-// LDS bit writer: bits LSB-first at an arbitrary start bit of a zeroed word
-// buffer; words shared with neighbouring lanes are merged with ds_or.  Only
-// words inside the window [w0, w0 + nw) are stored (buf points at word w0),
-// so a chunk larger than the LDS window is emitted in several passes.
-struct LdsBits {
-  uint32_t* buf;
-  uint32_t word;  // absolute word index of the word being filled
-  uint32_t nacc;
-  uint32_t w0, nw;
-  uint64_t acc;
-  __device__ __forceinline__ void init(uint32_t* b, uint32_t bitpos, uint32_t win0, uint32_t nwin) {
-    buf = b;
-    word = bitpos >> 5;
-    nacc = bitpos & 31u;
-    acc = 0;
-    w0 = win0;
-    nw = nwin;
-  }
-  __device__ __forceinline__ void emit_word(uint32_t v) {
-    const uint32_t k = word - w0;  // wraps to a large value below the window
-    if (k < nw && v != 0u) atomicOr(&buf[k], v);
-  }
-  // count <= 32, value holds only its low `count` bits
-  __device__ __forceinline__ void put(uint64_t value, uint32_t count) {
-    acc |= value << nacc;
-    nacc += count;
-    if (nacc >= 32) {
-      emit_word((uint32_t)acc);
-      ++word;
-      acc >>= 32;
-      nacc -= 32;
-    }
-  }
-  // count <= 64
-  __device__ __forceinline__ void put64(uint64_t value, uint32_t count) {
-    if (count > 32) {
-      put(value & 0xFFFFFFFFull, 32);
-      put(value >> 32, count - 32);
-    } else {
-      put(value, count);
-    }
-  }
-  __device__ __forceinline__ void flush() {
-    if (nacc > 0) emit_word((uint32_t)acc);
-  }
-};
-
 // unsqueeze, the inverse of squeeze: every set bit of m, at position k and
 // i-th from the bottom (i >= 1), moves to k + i (128-bit result lo | hi<<64).
 // Applied to the newly significant coefficients of a plane this gives the
@@ -296,43 +184,6 @@ __device__ __forceinline__ void unsqueeze64(uint64_t m, const uint16_t* tab, uin
     hi |= sh >= 64u ? v << (sh - 64u) : (sh > 48u ? v >> (64u - sh) : 0ull);
     c += (uint32_t)__builtin_popcount(b);
   }
-}
-
-// emit one plane with the group-testing coder, n = significant prefix: the
-// n verbatim bits, then the whole group-test section at once.  In the section
-// the i-th newly significant coefficient, at k past the prefix, puts its
-// terminator at bit k + i (unsqueeze); every terminator but the last is
-// followed by a positive test, bit 0 is the first test, and a negative test
-// ends the section.  When the last significant coefficient is coefficient 63
-// its terminator is implied and the section ends just before it.
-__device__ __forceinline__ void plane_emit(LdsBits& w, uint64_t wd, uint32_t& n, const uint16_t* tab) {
-  if (n > 0) w.put64(n == 64 ? wd : (wd & ((1ull << n) - 1ull)), n);
-  if (n >= 64) return;
-  const uint64_t rest = wd >> n;
-  if (rest == 0) {  // a single negative test
-    w.put(0, 1);
-    return;
-  }
-  const uint32_t top = 63u - (uint32_t)__builtin_clzll(rest);  // last new coefficient, past the prefix
-  const uint32_t lastt = top + (uint32_t)__builtin_popcountll(rest);  // its terminator's bit
-  uint64_t tlo, thi;
-  unsqueeze64(rest, tab, tlo, thi);
-  // positive tests: bit 0 and the bit after every terminator but the last
-  uint64_t slo = tlo | (tlo << 1) | 1ull, shi = thi | (thi << 1) | (tlo >> 63);
-  const bool implied = n + top == 63u;
-  // no positive test follows the last terminator (a negative test does,
-  // unless the terminator is implied: then it is dropped as well)
-  const uint32_t a = lastt + 1u;
-  if (a < 64u) slo &= ~(1ull << a);
-  else shi &= ~(1ull << (a - 64u));
-  if (implied) {
-    if (lastt < 64u) slo &= ~(1ull << lastt);
-    else shi &= ~(1ull << (lastt - 64u));
-  }
-  const uint32_t len = implied ? lastt : lastt + 2u;
-  w.put64(slo, len < 64u ? len : 64u);
-  if (len > 64u) w.put64(shi, len - 64u);
-  n += top + 1u;
 }
 
 // ---------------------------------------------------------------------------
@@ -613,26 +464,24 @@ template <class T> __device__ __forceinline__ int block_emax(typename FT<T>::U m
   return biased - FT<T>::BIAS + 1;
 }
 
-template <class T> __device__ __forceinline__ typename FT<T>::U to_nb(typename FT<T>::S q) {
-  typedef typename FT<T>::U U;
-  return ((U)q + FT<T>::NB) ^ FT<T>::NB;
-}
-template <class T> __device__ __forceinline__ typename FT<T>::S from_nb(typename FT<T>::U u) {
-  typedef typename FT<T>::S S;
-  return (S)((u ^ FT<T>::NB) - FT<T>::NB);
-}
-
-// residual block -> negabinary coefficients in coded order (u[r])
+// residual block -> coefficients in coded order, plus the negabinary mask M:
+// v = q + M, whose negabinary word is v ^ M.  Kept in this form because both
+// uses are cheaper from it: the integer that the top p planes stand for is
+// (v & m) - (M & m), m the planes' mask, and the planes' words take M's bits
+// out after the transpose, one xor for 32 coefficients.
 template <class T>
-__device__ __forceinline__ void forward_coeffs(const T e[64], int emax, typename FT<T>::U u[64]) {
+__device__ __forceinline__ void forward_coeffs_biased(const T e[64], int emax, typename FT<T>::U v[64]) {
   typedef typename FT<T>::S S;
+  typedef typename FT<T>::U U;
   S q[64];
 #pragma unroll
   for (int l = 0; l < 64; ++l) q[l] = (S)quantize(e[l], emax);
   xform_fwd(q);
 #pragma unroll
-  for (int r = 0; r < 64; ++r) u[r] = to_nb<T>(q[kOrder.at[r]]);
+  for (int r = 0; r < 64; ++r) v[r] = (U)q[kOrder.at[r]] + FT<T>::NB;
 }
+__device__ __forceinline__ uint32_t high_word(uint32_t v) { return v; }
+__device__ __forceinline__ uint32_t high_word(uint64_t v) { return (uint32_t)(v >> 32); }
 
 // the inverse transform: coded-order integers c (already out of negabinary)
 // -> block order, then the z and y passes ...
@@ -656,6 +505,18 @@ template <class T> __device__ __forceinline__ void inverse_x(typename FT<T>::S q
 #pragma unroll
   for (int r = 0; r < 16; ++r) lift_inv(q[4 * r], q[4 * r + 1], q[4 * r + 2], q[4 * r + 3]);
 }
+// the whole inverse transform of words in block order (z, y, x)
+template <class S> __device__ __forceinline__ void inverse_words(S q[64]) {
+#pragma unroll
+  for (int l = 0; l < 16; ++l) lift_inv(q[l], q[l + 16], q[l + 32], q[l + 48]);
+#pragma unroll
+  for (int l = 0; l < 16; ++l) {
+    const int b = 16 * (l >> 2) + (l & 3);
+    lift_inv(q[b], q[b + 4], q[b + 8], q[b + 12]);
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) lift_inv(q[4 * r], q[4 * r + 1], q[4 * r + 2], q[4 * r + 3]);
+}
 // While every nonzero q * 2^(emax-30) is a normal float (emax >= -96) and no
 // product overflows (emax <= 126), the int -> float conversion performs the
 // one rounding and the power-of-two scale is exact, so the product equals
@@ -664,22 +525,6 @@ template <class T> __device__ __forceinline__ void inverse_x(typename FT<T>::S q
 __device__ __forceinline__ bool fast_dequant(int emax) { return emax >= -96 && emax <= 126; }
 __device__ __forceinline__ float dequant_scale(int emax) {
   return __uint_as_float((uint32_t)(emax - 30 + 127) << 23);
-}
-// dv[l] * scale is the dequantised value, exactly (scale = 1 on the double route)
-__device__ __forceinline__ float dequantize_block(const int32_t q[64], int emax, float dv[64]) {
-  if (fast_dequant(emax)) {
-#pragma unroll
-    for (int l = 0; l < 64; ++l) dv[l] = (float)q[l];
-    return dequant_scale(emax);
-  }
-#pragma unroll
-  for (int l = 0; l < 64; ++l) dv[l] = dequantize(q[l], emax);
-  return 1.0f;
-}
-__device__ __forceinline__ double dequantize_block(const int64_t q[64], int emax, double dv[64]) {
-#pragma unroll
-  for (int l = 0; l < 64; ++l) dv[l] = dequantize(q[l], emax);
-  return 1.0;
 }
 __device__ __forceinline__ void dequant_add(const int32_t q[64], int emax, float acc[64]) {
   if (fast_dequant(emax)) {
@@ -724,7 +569,12 @@ template <> __device__ __forceinline__ double hi16_scale<double>(int emax) {
 }
 __device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
-template <class T> __device__ __forceinline__ void lift_dequant_add_hi16(v2s R[32], int emax, T acc[64]) {
+__device__ __forceinline__ float fmax_t(float a, float b) { return __builtin_fmaxf(a, b); }
+__device__ __forceinline__ double fmax_t(double a, double b) { return __builtin_fmax(a, b); }
+__device__ __forceinline__ float fabs_t(float a) { return __builtin_fabsf(a); }
+__device__ __forceinline__ double fabs_t(double a) { return __builtin_fabs(a); }
+// the z and y passes on pairs of adjacent x, R[m] = (h[2m], h[2m+1]) in block order
+__device__ __forceinline__ void lift_zy_hi16(v2s R[32]) {
 #pragma unroll
   for (int m = 0; m < 8; ++m) lift_inv(R[m], R[m + 8], R[m + 16], R[m + 24]);  // z: l, l+16, l+32, l+48
 #pragma unroll
@@ -732,22 +582,28 @@ template <class T> __device__ __forceinline__ void lift_dequant_add_hi16(v2s R[3
     const int m = 8 * (k >> 1) + (k & 1);
     lift_inv(R[m], R[m + 2], R[m + 4], R[m + 6]);
   }
+}
+// the x pass of rows 2s and 2s+1 (X[x] = (q[8s + x], q[8s + 4 + x])), as floating-point values
+template <class T> __device__ __forceinline__ void lift_x_hi16(const v2s R[32], int s, T d[8]) {
+  const uint32_t a0 = __builtin_bit_cast(uint32_t, R[4 * s]), a1 = __builtin_bit_cast(uint32_t, R[4 * s + 1]);
+  const uint32_t b0 = __builtin_bit_cast(uint32_t, R[4 * s + 2]), b1 = __builtin_bit_cast(uint32_t, R[4 * s + 3]);
+  v2s X0 = __builtin_bit_cast(v2s, __builtin_amdgcn_perm(b0, a0, 0x05040100u));
+  v2s X1 = __builtin_bit_cast(v2s, __builtin_amdgcn_perm(b0, a0, 0x07060302u));
+  v2s X2 = __builtin_bit_cast(v2s, __builtin_amdgcn_perm(b1, a1, 0x05040100u));
+  v2s X3 = __builtin_bit_cast(v2s, __builtin_amdgcn_perm(b1, a1, 0x07060302u));
+  lift_inv(X0, X1, X2, X3);
+  d[0] = (T)X0.x; d[1] = (T)X1.x; d[2] = (T)X2.x; d[3] = (T)X3.x;
+  d[4] = (T)X0.y; d[5] = (T)X1.y; d[6] = (T)X2.y; d[7] = (T)X3.y;
+}
+template <class T> __device__ __forceinline__ void lift_dequant_add_hi16(v2s R[32], int emax, T acc[64]) {
+  lift_zy_hi16(R);
   const T scale = hi16_scale<T>(emax);
 #pragma unroll
-  for (int s = 0; s < 8; ++s) {  // rows 2s and 2s+1: X[x] = (q[8s + x], q[8s + 4 + x])
-    const uint32_t a0 = __builtin_bit_cast(uint32_t, R[4 * s]), a1 = __builtin_bit_cast(uint32_t, R[4 * s + 1]);
-    const uint32_t b0 = __builtin_bit_cast(uint32_t, R[4 * s + 2]), b1 = __builtin_bit_cast(uint32_t, R[4 * s + 3]);
-    v2s X0 = __builtin_bit_cast(v2s, __builtin_amdgcn_perm(b0, a0, 0x05040100u));
-    v2s X1 = __builtin_bit_cast(v2s, __builtin_amdgcn_perm(b0, a0, 0x07060302u));
-    v2s X2 = __builtin_bit_cast(v2s, __builtin_amdgcn_perm(b1, a1, 0x05040100u));
-    v2s X3 = __builtin_bit_cast(v2s, __builtin_amdgcn_perm(b1, a1, 0x07060302u));
-    lift_inv(X0, X1, X2, X3);
-    const v2s X[4] = {X0, X1, X2, X3};
+  for (int s = 0; s < 8; ++s) {
+    T d[8];
+    lift_x_hi16<T>(R, s, d);
 #pragma unroll
-    for (int x = 0; x < 4; ++x) {
-      acc[8 * s + x] = fma_t((T)X[x].x, scale, acc[8 * s + x]);
-      acc[8 * s + 4 + x] = fma_t((T)X[x].y, scale, acc[8 * s + 4 + x]);
-    }
+    for (int t = 0; t < 8; ++t) acc[8 * s + t] = fma_t(d[t], scale, acc[8 * s + t]);
   }
 }
 // R[m] = (q[2m], q[2m+1]) in block order: high halves of the coded-order words c
@@ -760,61 +616,6 @@ __device__ __forceinline__ void pack_hi16(const int32_t c[64], v2s R[32]) {
 
 template <class U> __device__ __forceinline__ U plane_mask(int P, int p) {
   return p >= P ? ~(U)0 : ~(((U)1 << (P - p)) - (U)1);
-}
-
-// Plane words of one 16-plane group are kept in LDS, one column per lane:
-// word r of the calling lane at pw[r * 64] (plane base+r of coefficients
-// 0..31 in r, of 32..63 in 16+r), so the plane loops below run as ordinary
-// loops instead of 16 unrolled copies.
-template <class U> __device__ __forceinline__ void group_to_lds(const U u[64], int base, uint32_t* pw) {
-  uint32_t Tw[32];
-  plane_group(u, base, Tw);
-#pragma unroll
-  for (int r = 0; r < 32; ++r) pw[r * 64] = Tw[r];
-}
-// t-th plane from the top of the group
-__device__ __forceinline__ uint64_t lds_plane(const uint32_t* pw, int t) {
-  return (uint64_t)pw[(15 - t) * 64] | ((uint64_t)pw[(31 - t) * 64] << 32);
-}
-
-// bits of p planes from the top, plane words in registers (the closed-form
-// cost is short, so the 16-plane loop can be unrolled)
-template <class T> __device__ __forceinline__ uint32_t planes_cost_reg(const typename FT<T>::U u[64], int p) {
-  constexpr int P = FT<T>::P;
-  uint32_t n = 0, bits = 0;
-  for (int g = 0; 16 * g < p; ++g) {
-    uint32_t Tw[32];
-    plane_group(u, P - 16 * (g + 1), Tw);
-    const int tmax = p - 16 * g;
-#pragma unroll
-    for (int t = 0; t < 16; ++t) {
-      if (t < tmax) bits += plane_cost((uint64_t)Tw[15 - t] | ((uint64_t)Tw[31 - t] << 32), n);
-    }
-  }
-  return bits;
-}
-
-template <class T>
-__device__ __forceinline__ void planes_emit(LdsBits& w, const typename FT<T>::U u[64], int p, uint32_t* pw,
-                                            const uint16_t* tab) {
-  typedef typename FT<T>::U U;
-  constexpr int P = FT<T>::P;
-  // leading empty planes (no coefficient significant yet) are one 0 bit each:
-  // the writer only advances over them, and groups made of them are skipped
-  U any = 0;
-#pragma unroll
-  for (int l = 0; l < 64; ++l) any |= u[l];
-  int zl = any ? (sizeof(U) == 4 ? __builtin_clz((uint32_t)any) : __builtin_clzll((uint64_t)any)) : P;
-  zl = zl < p ? zl : p;
-  w.put64(0, (uint32_t)zl);
-  uint32_t n = 0;
-  // each lane starts at its own first non-empty plane, so the wave's loop
-  // runs max(p - zl) times rather than max(p) - min(zl)
-  for (int g = zl / 16; 16 * g < p; ++g) {
-    group_to_lds(u, P - 16 * (g + 1), pw);
-    const int tmax = p - 16 * g < 16 ? p - 16 * g : 16;
-    for (int t = 16 * g >= zl ? 0 : zl - 16 * g; t < tmax; ++t) plane_emit(w, lds_plane(pw, t), n, tab);
-  }
 }
 
 // Transpose of the plane words of W slots (W = 4, 8 or 16) into W-bit
@@ -1200,24 +1001,6 @@ template <class S> __device__ __forceinline__ uint32_t pq_width(const S q[64], b
 
 template <class T> __device__ __forceinline__ uint32_t pq_bits(int delta, uint32_t w) {
   return 2u + (uint32_t)(delta + 1) + 1u + 6u + 64u * w;
-}
-
-// emit a coded block of codec 1 (its header bits included)
-template <class T>
-__device__ __forceinline__ void pq_emit(LdsBits& w, typename FT<T>::S q[64], int delta, bool pred, uint32_t width) {
-  typedef typename FT<T>::U U;
-  w.put(1, 2);  // nonempty, coded
-  for (int t = 0; t < delta; ++t) w.put(1, 1);
-  w.put(0, 1);
-  w.put(pred ? 1u : 0u, 1);
-  w.put(width, 6);
-  if (pred) lorenzo_fwd(q);
-#pragma unroll
-  for (int l = 0; l < 64; ++l) {
-    const U z = zigzag(q[l]);
-    if constexpr (sizeof(U) == 4) w.put(z, width);
-    else w.put64(z, width);
-  }
 }
 
 // Alg. 2 for one block of codec 1: acc += x_i (left to right)

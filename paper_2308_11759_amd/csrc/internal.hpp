@@ -37,7 +37,7 @@ struct pmc_ctx {
   // allocated (the calls then read into pageable memory)
   void* pin = nullptr;
 };
-constexpr size_t kPinBytes = 8192;  // >= kMaxComps * sizeof(CompMeta)
+constexpr size_t kPinBytes = 16384;  // >= kMaxComps * sizeof(CompMeta), the partials of the range
 
 struct pmc_store {
   pmc_field f{};
@@ -58,6 +58,13 @@ pmc_status fail(pmc_ctx* ctx, pmc_status st, const char* fmt, ...);
 pmc_status hipfail(pmc_ctx* ctx, hipError_t e, const char* what);
 uint64_t elem_size(const pmc_field* f);
 uint64_t stream_cap_one(const pmc::Geo& g, int dtype);
+// device workspace for compressing one field into n components, without the
+// components' results (CompMeta), and its layout: fills the job's pointers
+// into ws (bytes of them) and its sizes; false if it does not fit
+uint64_t job_workspace(const pmc_field* f, const pmc::Geo& g, int n);
+// apart: for components in one launch each
+bool job_layout(const pmc_field* f, const pmc::Geo& g, int n, bool apart, uint8_t* ws, uint64_t bytes,
+                pmc::FieldJob* job);
 // a store from per-component device results (offsets relative to d_base)
 pmc_store* store_from_meta(const pmc_field* f, const pmc::Geo& g, int n, const double* tau, const int* minexp,
                            const pmc::CompMeta* hm, const uint8_t* d_base, int codec);

@@ -13,7 +13,8 @@ constexpr int kMaxDecode = 16;  // components decoded by one k_decode launch
 enum : unsigned int {
   FLAG_NONFINITE = 1u,  // NaN / Inf in the input field
   FLAG_OVERFLOW = 2u,   // stream capacity exceeded
-  FLAG_INDEX = 4u       // payload too large for 32-bit word offsets
+  FLAG_INDEX = 4u,      // payload too large for 32-bit word offsets
+  FLAG_STAGING = 8u     // a wave's staging slot was too small for every component
 };
 
 // per-component results kept on the device during compression
@@ -31,51 +32,58 @@ struct CompMeta {
 };
 static_assert(sizeof(CompMeta) == 128, "CompMeta layout");
 
-template <class T> struct EncArgs {
-  const T* x;
-  const T* xt_in;  // x~_{i-1} (not read for the first component)
-  T* xt_out;       // x~_i (not written for the last component); never xt_in
+// chunk offsets are an exclusive scan of chunk word counts, in tiles of
+// kPackTile chunks (64 encoder waves), one pack workgroup each
+constexpr int kPackTile = 256;
+// one tile's sums of one component
+struct TileRec {
+  unsigned long long words;   // payload words of the tile's chunks
+  unsigned long long before;  // ... of the tiles before it
+  unsigned long long linf;    // bits of the largest measured error
+  unsigned long long counts;  // empty, raw, escalated, missed blocks, 16 bits each
+  uint32_t stat;              // kStat* flags of any wave
+  uint32_t span;              // largest payload words of four consecutive chunks
+  unsigned long long pad[2];
+};
+static_assert(sizeof(TileRec) == 56, "TileRec layout");
+
+// one wave's record of one component (wave_stat): the counts of empty, raw,
+// escalated and missed blocks (7 bits each), then flags
+constexpr uint32_t kStatFull = 1u << 28;       // a coded block outside the float32 high-half decode route
+constexpr uint32_t kStatNonfinite = 1u << 29;  // NaN / Inf in the input
+constexpr uint32_t kStatOver = 1u << 30;       // the wave's slot was too small for this component
+
+// One field being compressed: components [comp0, comp1) in one launch.  The
+// encoder's waves (64 blocks, 4 chunks each) take their blocks through all of
+// them and leave each component's span of payload words in the wave's staging
+// slot, one behind the other; the pack moves the spans into the streams.
+struct FieldJob {
+  const void* x;
   Geo g;
-  double tau;
-  int minexp;
-  int first;  // x~_{i-1} = 0: not read
-  int last;   // x~_i not written
-  uint32_t* staging;
-  uint32_t* chunk_words;
-  uint32_t* aux;   // per block: bit offset of the block inside its chunk
-  CompMeta* meta;  // this component's entry
-  double* berr;    // per block: max error before this component (read unless first), after it (written unless last)
-  double h0, inv0;  // codec 1: the bin 2 tau and its reciprocal (computed on the host)
+  void* tiles;        // x~ of every wave between launches (64 * 64 values each), where components run one launch each
+  uint32_t* staging;  // wave w's slot at w * slot_words
+  uint32_t slot_words, slot_last;  // words of a slot, of the last wave's
+  uint32_t* chunk_words;  // [component][chunk]
+  double* wave_linf;      // [component][wave] largest measured error
+  uint32_t* wave_stat;    // [component][wave]
+  uint32_t* wave_start;   // [component][wave] first word of the span in its slot; none for one component (0)
+  TileRec* tile_recs;     // [component][tile]
+  CompMeta* meta;         // [component], written by the pack's bookkeeping
+  CompMeta* host_meta;    // the same in pinned host memory (may be null)
+  uint8_t* region;        // the stream region: block indexes, then streams
+  unsigned long long region_cap;
+  uint64_t aux_stride;    // block index of component i at region + 4 * i * aux_stride
+  uint8_t ncomp, comp0, comp1;
+  uint8_t dtype, codec;   // dtype 1 = f32, 2 = f64
+  uint8_t pad[3];
+  double tau[kMaxComps];
+  int32_t minexp[kMaxComps];
 };
-
-// chunk offsets are an exclusive scan of chunk word counts, done in tiles of
-// kScanTile chunks: tile sums, a scan of the tile sums, then per-tile scans
-constexpr int kScanTile = 1024;
-
-struct ScanArgs {
-  const uint32_t* chunk_words;
-  uint32_t* offsets;
-  unsigned long long* tile_sums;  // ceil(nchunks / kScanTile) entries
-  uint64_t nchunks;
-  uint64_t aux_bytes;  // device bytes of one component's block index (256-aligned)
-  CompMeta* meta;      // all components
-  int comp, ncomp;
-  unsigned long long streams_cap;
-};
-
-struct PackArgs {
-  const uint32_t* staging;
-  const uint32_t* chunk_words;
-  const uint32_t* offsets;
-  uint64_t nchunks;
-  CompMeta* meta;  // the pack records each component's largest decode-wave span
-  int comp;
-  int minexp;
-  uint8_t* streams;
-  Geo g;
-  double tau;
-  int codec;  // written into the stream header
-};
+static_assert(sizeof(FieldJob) == 576, "a batch's table has its place in the workspace");
+template <class F> __host__ __device__ inline uint32_t job_waves(const F& f) { return (uint32_t)((f.g.nblocks + 63) / 64); }
+template <class F> __host__ __device__ inline uint32_t job_tiles(const F& f) {
+  return (uint32_t)((f.g.nchunks + kPackTile - 1) / kPackTile);
+}
 
 template <class T> struct DecArgs {
   const uint8_t* s[kMaxDecode];    // stream starts
@@ -137,56 +145,30 @@ struct AuxArgs {
   unsigned long long* full;  // optional (NULL): set when a coded block is outside the float32 high-half route
 };
 
-// ---- batches of fields (one table entry per field) -----------------------
-struct FieldDev {
-  const void* x;
-  void* xt[2];  // x~ ping-pong: component i reads xt[(i-1)&1], writes xt[i&1]
-  Geo g;
-  uint32_t* staging;
-  uint32_t* chunk_words;
-  uint32_t* offsets;
-  unsigned long long* tile_sums;
-  uint32_t* aux0;           // block index of component 0; component i at aux0 + i * aux_stride
-  uint64_t aux_stride;      // in 32-bit words
-  CompMeta* meta0;          // meta of component 0; component i at meta0 + i
-  double* berr;             // per-block error carried between components
-  uint8_t* region;          // the field's stream region: block indexes, then streams
-  unsigned long long region_cap;
-  int ncomp;
-  int dtype;                // 1 = f32, 2 = f64
-  uint32_t ntiles;          // scan tiles of the field
-  uint32_t pad;
-  double tau[kMaxComps];
-  int minexp[kMaxComps];
-};
-
-struct Item {  // (field, group) : a wave of 64 blocks, a scan tile, or 4 chunks
+struct Item {  // (field, group): a wave of 64 blocks or a pack tile
   uint32_t field, index;
 };
 
 struct BatchArgs {
-  const FieldDev* fields;
+  const FieldJob* fields;
   uint32_t nfields;
-  const Item* items;  // encode waves of one dtype, scan tiles or chunk quads
+  const Item* items;  // encode waves of one dtype, or pack tiles
   uint32_t nitems;
-  int comp;
 };
 
+// every component of a field (job.codec 0 or 1), then the scan and pack of its streams
+template <class T> hipError_t launch_encode(const FieldJob& f, hipStream_t s);
+hipError_t launch_pack(const FieldJob& f, hipStream_t s);
+// the same for a batch (comps: the most components [comp0, comp1) of any field)
 template <class T> hipError_t launch_encode_batch(const BatchArgs& a, uint32_t grid, hipStream_t s);
-hipError_t launch_batch_scan(const BatchArgs& tiles, uint32_t nfields, hipStream_t s);
-hipError_t launch_batch_pack(const BatchArgs& quads, hipStream_t s);
-hipError_t launch_batch_init(const FieldDev* fields, uint32_t nfields, hipStream_t s);
+hipError_t launch_batch_pack(const BatchArgs& tiles, uint32_t comps, hipStream_t s);
 
-// codec: 0 the block-transform codec, 1 prediction and quantisation
-template <class T> hipError_t launch_encode(const EncArgs<T>& a, int codec, hipStream_t s);
-hipError_t launch_scan(const ScanArgs& a, hipStream_t s);
 template <class T> hipError_t launch_aux(const AuxArgs& a, int codec, hipStream_t s);
 // max_span: the largest word span of a wave's four chunks over the decoded
 // streams; spans up to the LDS staging capacity use the staged kernel
 // hires: as launch_decode's, for every query of the launch
 template <class T>
 hipError_t launch_decode_queries(const ServeArgs& a, uint64_t max_span, int codec, bool hires, hipStream_t s);
-template <class T> hipError_t launch_pack(const PackArgs& a, hipStream_t s);
 // hires: every residual component of the launch (store index > 0) has no
 // block outside the float32 high-half route (CompMeta.full == 0), so the
 // decoder may run them on that route alone
@@ -199,7 +181,7 @@ uint64_t stage_words();  // capacity of the decoder's LDS staging buffer, in wor
 // min / max / non-finite count of n samples: one partial of kRangeWords words
 // per workgroup at out; range_groups: how many workgroups suit n, at most
 // max_groups
-constexpr uint32_t kRangeWords = 3, kRangeGroups = 256;
+constexpr uint32_t kRangeWords = 3, kRangeGroups = 512;
 uint32_t range_groups(uint64_t n, uint64_t max_groups);
 template <class T>
 hipError_t launch_range(const T* x, uint64_t n, unsigned long long* out, uint32_t groups, hipStream_t s);
