@@ -832,18 +832,21 @@ pmc_status pmc_store_deserialize(pmc_ctx* ctx, const void* host_buf, size_t size
   if (e == hipSuccess)
     e = hipMemcpyAsync(base + v.n * auxb, region, v.region_bytes, hipMemcpyHostToDevice, ctx->stream);
   // rebuild the per-block index of every stream
-  for (int i = 0; i < v.n && e == hipSuccess; ++i) {
-    AuxArgs a{};
-    a.s = base + s->offset[i];
-    a.aux = (uint32_t*)(base + s->aux_offset[i]);
-    a.words = s->words[i];
-    a.minexp = s->minexp[i];
-    a.g = g;
-    a.status = status;
-    a.full = full + i;
-    e = s->f.dtype == PMC_F32 ? launch_aux<float>(a, s->codec, ctx->stream)
-                              : launch_aux<double>(a, s->codec, ctx->stream);
+  AuxArgs a{};
+  uint64_t span = 0;
+  for (int i = 0; i < v.n; ++i) {
+    a.s[i] = base + s->offset[i];
+    a.aux[i] = (uint32_t*)(base + s->aux_offset[i]);
+    a.words[i] = s->words[i];
+    a.minexp[i] = s->minexp[i];
+    span = std::max(span, spans[i]);
   }
+  a.g = g;
+  a.status = status;
+  a.full = full;
+  if (e == hipSuccess)
+    e = s->f.dtype == PMC_F32 ? launch_aux<float>(a, v.n, span, s->codec, ctx->stream)
+                              : launch_aux<double>(a, v.n, span, s->codec, ctx->stream);
   unsigned long long trailer[1 + kMaxComps] = {};
   if (e == hipSuccess)
     e = hipMemcpyAsync(trailer, status, 8 * (1 + (size_t)v.n), hipMemcpyDeviceToHost, ctx->stream);

@@ -242,6 +242,13 @@ struct GBits {
     refill();
     drop(count);
   }
+  __device__ __forceinline__ void skip64(uint32_t count) {  // count <= 64
+    if (count > 32) {
+      skip(32);
+      count -= 32;
+    }
+    skip(count);
+  }
   __device__ __forceinline__ uint32_t peek32() {  // the next 32 bits
     refill();
     return (uint32_t)buf;
@@ -290,6 +297,7 @@ struct LBits {
     o = t & 31u;
     load();
   }
+  __device__ __forceinline__ void skip64(uint32_t count) { skip(count); }
   __device__ __forceinline__ uint32_t get(uint32_t count) {  // count <= 32
     const uint32_t v = peek32();
     skip(count);
@@ -877,6 +885,47 @@ template <class T> __device__ __forceinline__ bool hi16_block(int p, int emax) {
   return sizeof(T) == 4 && p <= 10 && fast_dequant(emax);
 }
 
+// advance a reader over one plane: plane_read without the plane's bits.  A
+// window's new coefficients reach as far as its last terminator less the
+// number of terminators up to it, so the squeeze is only needed where that
+// passes coefficient 62 (a run that reaches the last coefficient).
+template <class R> __device__ __forceinline__ void plane_skip(R& r, uint32_t& n, const uint8_t* sq) {
+  if (n > 0) r.skip64(n);
+  uint32_t vg = 0;
+  while (n < 64) {
+    const uint32_t s = (r.peek32() << vg) | vg;
+    const bool neg = (s & 1u) == 0u;
+    const uint32_t term = terminators(s);
+    const uint32_t ends = term & ~(s >> 1) & 0x7FFFFFFFu;
+    const uint32_t last = (uint32_t)__builtin_ctz(ends | 0x80000000u);
+    const uint32_t tm = neg ? 0u : term & ((2u << last) - 1u);
+    const uint32_t room = 63u - n;
+    uint32_t cnt = (uint32_t)__builtin_popcount(tm);
+    uint32_t nn = tm ? 32u - (uint32_t)__builtin_clz(tm) - cnt : 0u;
+    bool tokens = tm != 0u;
+    if (nn > room) {
+      const uint32_t vrel = __builtin_amdgcn_ubfe(squeeze32(tm, sq), 0u, room < 31u ? room : 31u);
+      tokens = false;
+      nn = 31u - (uint32_t)__builtin_clz((vrel << 1) | 1u);
+      cnt = (uint32_t)__builtin_popcount(vrel);
+    }
+    const uint32_t g = nn + cnt;
+    n += nn;
+    const uint32_t z = 63u - n;
+    const bool run = !neg && !tokens;
+    const bool implied = run && z <= 31u - g;
+    const bool done = neg || implied || (tokens && ends != 0u);
+    const uint32_t c_tok = g + (ends != 0u ? 1u : 0u);
+    const uint32_t c_run = implied ? g + 1u + z : 32u;
+    const uint32_t c_any = tokens ? c_tok : c_run;
+    const uint32_t c = neg ? 1u : c_any;
+    r.skip(c - vg);
+    n = implied ? 64u : run ? n + 31u - g : n;
+    vg = run ? 1u : 0u;
+    if (done) break;
+  }
+}
+
 // advance a reader over one block without reconstructing it; returns false
 // on a malformed header.  full: set for a coded block outside the float32
 // high-half route (hi16_block)
@@ -886,7 +935,7 @@ __device__ __forceinline__ bool block_skip(R& r, int minexp, const uint8_t* sq, 
   constexpr int P = FT<T>::P;
   if (!r.get(1)) return true;  // empty
   if (r.get(1)) {              // raw
-    for (int l = 0; l < 64; ++l) r.get64((uint32_t)P);
+    for (int l = 0; l < P; ++l) r.skip64(64);
     return true;
   }
   int delta = 0;
@@ -899,8 +948,12 @@ __device__ __forceinline__ bool block_skip(R& r, int minexp, const uint8_t* sq, 
   p = (p < 0 ? 0 : (p > P ? P : p)) + delta;
   if (emax < 2 - FT<T>::BIAS || p < 1 || p > P) return false;
   full = sizeof(T) == 4 && !hi16_block<T>(p, emax);
+  // leading empty planes (one 0 each) at once
+  const int z0 = (int)__builtin_ctz(r.peek32() | 0x80000000u);
+  const int zlead = z0 < p ? z0 : p;
+  r.skip64((uint32_t)zlead);
   uint32_t n = 0;
-  for (int t = 0; t < p; ++t) (void)plane_read(r, n, sq);
+  for (int t = zlead; t < p; ++t) plane_skip(r, n, sq);
   return true;
 }
 
@@ -1057,7 +1110,7 @@ template <class T, class R> __device__ __forceinline__ bool pq_block_skip(R& r) 
   constexpr int P = FT<T>::P;
   if (!r.get(1)) return true;
   if (r.get(1)) {
-    for (int l = 0; l < 64; ++l) r.get64((uint32_t)P);
+    for (int l = 0; l < P; ++l) r.skip64(64);
     return true;
   }
   int delta = 0;
@@ -1068,7 +1121,7 @@ template <class T, class R> __device__ __forceinline__ bool pq_block_skip(R& r) 
   r.get(1);
   const uint32_t width = r.get(6);
   if (width > (uint32_t)P) return false;  // a P-bit zigzag value needs at most P bits
-  for (int l = 0; l < 64; ++l) r.get64(width);
+  for (uint32_t l = 0; l < width; ++l) r.skip64(64);
   return true;
 }
 

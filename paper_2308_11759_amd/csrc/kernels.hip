@@ -14,31 +14,76 @@
 namespace pmc {
 
 // ---------------------------------------------------------------------------
-// per-block bit offsets of a stream written elsewhere: parse each chunk
-template <class T, int kCodec>
-__global__ __launch_bounds__(64) void k_aux(AuxArgs a) {
-  __shared__ uint8_t s_squeeze[256];
-  squeeze_table(s_squeeze);
-  const uint64_t chunk = (uint64_t)blockIdx.x * 64 + threadIdx.x;
-  if (chunk >= a.g.nchunks) return;
-  const uint32_t* index = reinterpret_cast<const uint32_t*>(a.s + kHeaderBytes);
-  const uint32_t* payload = index + a.g.nchunks;
-  const uint64_t start = index[chunk];
-  const uint64_t stop = chunk + 1 < a.g.nchunks ? (uint64_t)index[chunk + 1] : a.words;
-  // a chunk holds at least one block, hence at least one bit
-  bool ok = start < stop && stop <= a.words && stop <= 0xFFFFFFFFull;
-  GBits r;
-  r.init(payload, (uint32_t)start, (uint32_t)(ok ? stop : start));
+// Per-block bit offsets of streams written elsewhere: each chunk's 16 blocks are
+// parsed one after the other by one lane, a serial chain, so latency and the
+// chains in flight are what counts.  A wave stages the words of L chunks in LDS
+// and L of its lanes parse them; all components go in one launch.  Few chunks
+// per wave keep the lanes' loops short (the wave takes as many windows as its
+// slowest lane) and the waves many: L = 4 while that leaves at most 4 waves
+// per SIMD (64^3 float64, 4 components: 68 us, 90 with L = 16), 16 beyond
+// (256^3 float32, 8 components: 218 us, 304 with L = 8; the upload of such a
+// store takes 3 ms).  One launch per component with 64 chunks per wave read
+// from global memory had 51 waves in flight for 3 M values and took 145 us per
+// component; all 6 take 91 us now.  L = 64: unstaged, for an index whose chunks are longer than any
+// encoder writes (which a loader may still be given).
+template <class T, int kCodec, class R>
+__device__ __forceinline__ void aux_chunk(const AuxArgs& a, int comp, uint64_t chunk, R& r, uint32_t from, bool ok,
+                                          const uint8_t* sq) {
   const uint64_t b0 = chunk * kChunkBlocks, b1 = min<uint64_t>(a.g.nblocks, b0 + kChunkBlocks);
+  const int minexp = a.minexp[comp];
+  uint32_t* const aux = a.aux[comp];
   bool any_full = false;
+#pragma unroll 1
   for (uint64_t blk = b0; blk < b1; ++blk) {
-    a.aux[blk] = ok ? (uint32_t)r.consumed((uint32_t)start) : 0u;
+    aux[blk] = ok ? (uint32_t)r.consumed(from) : 0u;
     bool full = false;
-    if (ok) ok = (kCodec == 0 ? block_skip<T>(r, a.minexp, s_squeeze, full) : pq_block_skip<T>(r)) && !r.bad();
+    if (ok) ok = (kCodec == 0 ? block_skip<T>(r, minexp, sq, full) : pq_block_skip<T>(r)) && !r.bad();
     any_full = any_full || full;
   }
-  if (!ok && a.status) atomicOr(a.status, 1u);
-  if (any_full && a.full && *(volatile unsigned long long*)a.full == 0) atomicOr(a.full, 1ull);
+  if (!ok) atomicOr(a.status, 1u);
+  if (any_full && *(volatile unsigned long long*)(a.full + comp) == 0) atomicOr(a.full + comp, 1ull);
+}
+template <class T, int kCodec, int L>
+__global__ __launch_bounds__(64) void k_aux(AuxArgs a) {
+  extern __shared__ uint32_t s_words[];  // a.cap words in rows of 64, and three more
+  __shared__ uint8_t s_squeeze[256];
+  const int comp = (int)blockIdx.y;
+  const uint32_t lane = threadIdx.x;
+  const uint32_t* index = reinterpret_cast<const uint32_t*>(a.s[comp] + kHeaderBytes);
+  const uint32_t* payload = index + a.g.nchunks;
+  const uint64_t words = a.words[comp];
+  const uint64_t c0 = (uint64_t)blockIdx.x * L, c1 = min<uint64_t>(c0 + L, a.g.nchunks);
+  uint64_t w0 = 0, w1 = words;
+  bool ok = true;
+  if constexpr (L < 64) {
+    w0 = index[c0];
+    w1 = c1 < a.g.nchunks ? (uint64_t)index[c1] : words;
+    ok = w0 <= w1 && w1 <= words && w1 - w0 <= a.cap;  // (so checked on the host)
+    const uint32_t span = ok ? (uint32_t)(w1 - w0) : 0u;
+    for (uint32_t k = 0; k < span; k += 64) {
+      const uint32_t j = k + lane < span ? k + lane : span - 1;
+      __builtin_amdgcn_global_load_lds((gmem_void_t*)(payload + w0 + j), (lds_void_t*)(s_words + k), 4, 0, 0);
+    }
+  }
+  squeeze_table(s_squeeze);
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  const uint64_t chunk = c0 + lane;
+  if (lane >= (uint32_t)L || chunk >= c1) return;
+  const uint64_t start = index[chunk];
+  const uint64_t stop = chunk + 1 < a.g.nchunks ? (uint64_t)index[chunk + 1] : words;
+  // a chunk holds at least one block, hence at least one bit
+  ok = ok && w0 <= start && start < stop && stop <= w1 && stop <= 0xFFFFFFFFull;
+  if constexpr (L < 64) {
+    LBits r;
+    const uint32_t from = ok ? (uint32_t)(start - w0) : 0u;
+    r.init(s_words, from, ok ? (uint32_t)(stop - w0) : 0u, a.cap);
+    aux_chunk<T, kCodec>(a, comp, chunk, r, from, ok, s_squeeze);
+  } else {
+    GBits r;
+    r.init(payload, (uint32_t)start, (uint32_t)(ok ? stop : start));
+    aux_chunk<T, kCodec>(a, comp, chunk, r, (uint32_t)start, ok, s_squeeze);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -309,10 +354,25 @@ template hipError_t launch_cast_encode<double>(const double*, uint64_t, int, flo
 template hipError_t launch_cast_decode<float>(const float*, uint64_t, int, float*, hipStream_t);
 template hipError_t launch_cast_decode<double>(const float*, uint64_t, int, double*, hipStream_t);
 
-template <class T> hipError_t launch_aux(const AuxArgs& a, int codec, hipStream_t s) {
-  const uint64_t wgs = (a.g.nchunks + 63) / 64;
-  if (codec == 0) hipLaunchKernelGGL((k_aux<T, 0>), dim3((uint32_t)wgs), dim3(64), 0, s, a);
-  else hipLaunchKernelGGL((k_aux<T, 1>), dim3((uint32_t)wgs), dim3(64), 0, s, a);
+template <class T, int kCodec> void launch_aux_codec(AuxArgs a, int ncomp, uint64_t max_span, hipStream_t s) {
+  constexpr uint64_t kWaves = 4 * 1024;  // 4 per SIMD
+  constexpr uint64_t kLds = 48 * 1024;   // (four chunks of raw float64 blocks: 33 KiB)
+  auto bytes = [](uint64_t words) { return ((words + 63) / 64 * 64 + 3) * 4; };
+  auto grid = [&](uint64_t l) { return dim3((uint32_t)((a.g.nchunks + l - 1) / l), (uint32_t)ncomp); };
+  if ((a.g.nchunks + 3) / 4 * (uint64_t)ncomp > kWaves && bytes(4 * max_span) <= kLds) {
+    a.cap = (uint32_t)(4 * max_span);
+    hipLaunchKernelGGL((k_aux<T, kCodec, 16>), grid(16), dim3(64), (uint32_t)bytes(a.cap), s, a);
+  } else if (bytes(max_span) <= kLds) {
+    a.cap = (uint32_t)max_span;
+    hipLaunchKernelGGL((k_aux<T, kCodec, 4>), grid(4), dim3(64), (uint32_t)bytes(a.cap), s, a);
+  } else {
+    a.cap = 0;
+    hipLaunchKernelGGL((k_aux<T, kCodec, 64>), grid(64), dim3(64), (uint32_t)bytes(0), s, a);
+  }
+}
+template <class T> hipError_t launch_aux(AuxArgs a, int ncomp, uint64_t max_span, int codec, hipStream_t s) {
+  if (codec == 0) launch_aux_codec<T, 0>(a, ncomp, max_span, s);
+  else launch_aux_codec<T, 1>(a, ncomp, max_span, s);
   return hipGetLastError();
 }
 uint32_t range_groups(uint64_t n, uint64_t max_groups) {
@@ -335,8 +395,8 @@ hipError_t launch_fill64_one(unsigned long long* p, uint64_t n, unsigned long lo
   return hipGetLastError();
 }
 
-template hipError_t launch_aux<float>(const AuxArgs&, int, hipStream_t);
-template hipError_t launch_aux<double>(const AuxArgs&, int, hipStream_t);
+template hipError_t launch_aux<float>(AuxArgs, int, uint64_t, int, hipStream_t);
+template hipError_t launch_aux<double>(AuxArgs, int, uint64_t, int, hipStream_t);
 template hipError_t launch_range<float>(const float*, uint64_t, unsigned long long*, uint32_t, hipStream_t);
 template hipError_t launch_range<double>(const double*, uint64_t, unsigned long long*, uint32_t, hipStream_t);
 template hipError_t launch_sum_sq<float>(const float*, const float*, double, uint64_t, double*, double*, hipStream_t);

@@ -134,15 +134,16 @@ struct ServeArgs {
   unsigned int* status;
 };
 
-// rebuild the per-block bit offsets of one stream (one lane per chunk)
+// rebuild the per-block bit offsets of a store's streams
 struct AuxArgs {
-  const uint8_t* s;
-  uint32_t* aux;
-  uint64_t words;
-  int minexp;
+  const uint8_t* s[kMaxComps];
+  uint32_t* aux[kMaxComps];
+  uint64_t words[kMaxComps];
+  int minexp[kMaxComps];
   Geo g;
-  unsigned int* status;  // optional (NULL): set when a chunk fails to parse
-  unsigned long long* full;  // optional (NULL): set when a coded block is outside the float32 high-half route
+  uint32_t cap;  // words a wave's chunks can have
+  unsigned int* status;  // set when a chunk fails to parse
+  unsigned long long* full;  // [component] set when a coded block is outside the float32 high-half route
 };
 
 struct Item {  // (field, group): a wave of 64 blocks or a pack tile
@@ -163,7 +164,9 @@ hipError_t launch_pack(const FieldJob& f, hipStream_t s);
 template <class T> hipError_t launch_encode_batch(const BatchArgs& a, uint32_t grid, hipStream_t s);
 hipError_t launch_batch_pack(const BatchArgs& tiles, uint32_t comps, hipStream_t s);
 
-template <class T> hipError_t launch_aux(const AuxArgs& a, int codec, hipStream_t s);
+// ncomp streams at once; max_span: the most payload words of four consecutive
+// chunks (aligned to four) of any of them
+template <class T> hipError_t launch_aux(AuxArgs a, int ncomp, uint64_t max_span, int codec, hipStream_t s);
 // max_span: the largest word span of a wave's four chunks over the decoded
 // streams; spans up to the LDS staging capacity use the staged kernel
 // hires: as launch_decode's, for every query of the launch

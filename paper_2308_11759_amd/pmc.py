@@ -332,9 +332,9 @@ class Context:
 
     def deserialize(self, blob, streams=None):
         """Rebuild a store from bytes written by Store.serialize (or any valid blob)."""
-        blob = bytes(blob)
+        blob = bytes(blob)  # (no copy of a bytes object, whose own memory is passed on)
         need = ctypes.c_size_t()
-        buf = ctypes.create_string_buffer(blob, len(blob))
+        buf = ctypes.cast(ctypes.c_char_p(blob), _vp)
         self._check(self.lib.pmc_store_device_bytes(buf, len(blob), ctypes.byref(need)), ctx=None)
         if streams is None:
             streams = torch.empty(max(need.value, 256), dtype=torch.uint8, device=self.device)
