@@ -625,11 +625,8 @@ static pmc_status decode_range(pmc_ctx* ctx, const pmc_store* s, int k0, int k1,
   for (int i0 = k0; i0 < k1; i0 += group) {
     const int i1 = i0 + group < k1 ? i0 + group : k1;
     uint64_t span = 0;
-    bool hires = true;  // every residual component's blocks on the high-half route
-    for (int i = i0; i < i1; ++i) {
-      span = std::max(span, s->max_span[i]);
-      if (i > 0 && s->full[i] != 0) hires = false;
-    }
+    for (int i = i0; i < i1; ++i) span = std::max(span, s->max_span[i]);
+    const bool hires = high_half(s, i0, i1) && (i0 > 0 || !in);
     if (s->f.dtype == PMC_F32) {
       DecArgs<float> a{};
       fill_decode_args(s, i0, i1, a);
@@ -647,7 +644,7 @@ static pmc_status decode_range(pmc_ctx* ctx, const pmc_store* s, int k0, int k1,
       a.g = s->g;
       a.status = status;
       ProfScope ps(ctx, s->codec == 0 ? "k_decode_f64" : "k_decode_pq_f64");
-      e = launch_decode<double>(a, span, s->codec, false, ctx->stream);
+      e = launch_decode<double>(a, span, s->codec, hires, ctx->stream);
     }
     if (e != hipSuccess) return hipfail(ctx, e, "decode");
     in = d_out;

@@ -17,6 +17,8 @@
 
 #include <type_traits>
 
+#include "launch.hpp"  // the decode route flags
+
 namespace pmc {
 
 constexpr int kVals = 64;         // values per block
@@ -780,15 +782,13 @@ __device__ __forceinline__ void planes_read(R& r, typename FT<T>::S c[64], int p
 // conversion and a power-of-two scale while the result is normal (the caller
 // checks emax >= -992), which is the value dequantize() gives.
 template <int W, class R>
-__device__ __forceinline__ void decode_hi32(R& r, int p, int zlead, int emax, double acc[64], const uint8_t* sq,
-                                            bool rel) {
+__device__ __forceinline__ void coeffs_hi32(R& r, int p, int zlead, int32_t c[64], const uint8_t* sq, bool rel) {
   uint32_t A[2 * W], n;
   const int base = read_slots<double, W>(r, A, p, zlead, sq, rel, n);
   const int sh32 = 32 - W - base;  // sh - 32
   const uint32_t MM = (sh32 & 1) ? 0x55555555u : 0xAAAAAAAAu;
   constexpr uint32_t kSlice = (1u << W) - 1u;
   const uint32_t off = opaque(0u - ((MM & kSlice) << sh32));
-  int32_t c[64];
 #pragma unroll
   for (int i = 0; i < W; ++i) {
     const uint32_t xl = A[i] ^ MM, xh = A[W + i] ^ MM;
@@ -812,20 +812,23 @@ __device__ __forceinline__ void decode_hi32(R& r, int p, int zlead, int emax, do
       }
     }
   }
-  int32_t q[64];
+}
+// the block's words h (q = h * 2^32) in block order
+template <int W, class R>
+__device__ __forceinline__ void words_hi32(R& r, int p, int zlead, int32_t h[64], const uint8_t* sq, bool rel) {
+  int32_t c[64];
+  coeffs_hi32<W>(r, p, zlead, c, sq, rel);
 #pragma unroll
-  for (int r2 = 0; r2 < 64; ++r2) q[kOrder.at[r2]] = c[r2];
+  for (int k = 0; k < 64; ++k) h[kOrder.at[k]] = c[k];
+  inverse_words(h);
+}
+template <int W, class R>
+__device__ __forceinline__ void decode_hi32(R& r, int p, int zlead, int emax, double acc[64], const uint8_t* sq,
+                                            bool rel) {
+  int32_t h[64];
+  words_hi32<W>(r, p, zlead, h, sq, rel);
 #pragma unroll
-  for (int l = 0; l < 16; ++l) lift_inv(q[l], q[l + 16], q[l + 32], q[l + 48]);
-#pragma unroll
-  for (int l = 0; l < 16; ++l) {
-    const int b = 16 * (l >> 2) + (l & 3);
-    lift_inv(q[b], q[b + 4], q[b + 8], q[b + 12]);
-  }
-#pragma unroll
-  for (int r2 = 0; r2 < 16; ++r2) lift_inv(q[4 * r2], q[4 * r2 + 1], q[4 * r2 + 2], q[4 * r2 + 3]);
-#pragma unroll
-  for (int l = 0; l < 64; ++l) acc[l] = acc[l] + __builtin_ldexp((double)q[l], emax - 30);
+  for (int l = 0; l < 64; ++l) acc[l] = acc[l] + __builtin_ldexp((double)h[l], emax - 30);
 }
 
 // The high-half route straight from the slots of a residual component (W =
@@ -878,11 +881,13 @@ __device__ __forceinline__ void slots_hi16(R& r, int p, int zlead, const uint8_t
   }
 }
 
-// a coded float32 block decodes on the high-half route (lift_dequant_add_hi16)
-// when its coded planes all lie in the top ten bit positions and its
-// exponent keeps the scaled values normal
-template <class T> __device__ __forceinline__ bool hi16_block(int p, int emax) {
-  return sizeof(T) == 4 && p <= 10 && fast_dequant(emax);
+// what a coded block asks of the decode routes: kNotHi16 when it is outside the
+// high-half route (lift_dequant_add_hi16: its planes in the top ten bit
+// positions, its exponent keeping the scaled values normal), kNotHi32 when a
+// float64 block is outside the high-word route (decode_hi32)
+template <class T> __device__ __forceinline__ uint32_t route_flags(int p, int emax) {
+  if constexpr (sizeof(T) == 4) return p <= 10 && fast_dequant(emax) ? 0u : kNotHi16;
+  else return (p <= 10 && emax >= -1008 ? 0u : kNotHi16) | (p <= 26 && emax >= -992 ? 0u : kNotHi32);
 }
 
 // advance a reader over one plane: plane_read without the plane's bits.  A
@@ -927,14 +932,14 @@ template <class R> __device__ __forceinline__ void plane_skip(R& r, uint32_t& n,
 }
 
 // advance a reader over one block without reconstructing it; returns false
-// on a malformed header.  full: set for a coded block outside the float32
-// high-half route (hi16_block)
+// on a malformed header.  flags: what the block asks of the decode routes
 template <class T, class R>
-__device__ __forceinline__ bool block_skip(R& r, int minexp, const uint8_t* sq, bool& full) {
-  full = false;
+__device__ __forceinline__ bool block_skip(R& r, int minexp, const uint8_t* sq, uint32_t& flags) {
+  flags = 0;
   constexpr int P = FT<T>::P;
   if (!r.get(1)) return true;  // empty
   if (r.get(1)) {              // raw
+    if (sizeof(T) == 8) flags = kHasRaw;
     for (int l = 0; l < P; ++l) r.skip64(64);
     return true;
   }
@@ -947,7 +952,7 @@ __device__ __forceinline__ bool block_skip(R& r, int minexp, const uint8_t* sq, 
   int p = emax - minexp + kGuard;
   p = (p < 0 ? 0 : (p > P ? P : p)) + delta;
   if (emax < 2 - FT<T>::BIAS || p < 1 || p > P) return false;
-  full = sizeof(T) == 4 && !hi16_block<T>(p, emax);
+  flags = route_flags<T>(p, emax);
   // leading empty planes (one 0 each) at once
   const int z0 = (int)__builtin_ctz(r.peek32() | 0x80000000u);
   const int zlead = z0 < p ? z0 : p;

@@ -19,12 +19,49 @@ namespace pmc {
 // high-word route where it applies); kRouteFull the plain route; kRouteHi16
 // the float32 high-half route, for components whose every block has p <= 10
 // and fast_dequant(emax) (the caller guarantees it)
-constexpr int kRouteAuto = 0, kRouteFull = 1, kRouteHi16 = 2;
+// float64 fields whose blocks qualify decode in 256 registers, two waves per
+// SIMD: kRouteHi16 for the residual components (p <= 10 and emax >= -1008),
+// kRouteFirst for a store's first one (no raw blocks, p <= 26 and emax >= -992).
+// x~ takes 128 of the registers, so with every route in one loop only one wave
+// fits and its LDS latency stands open: 256^3, k = 8, 201 us, now 131.
+constexpr int kRouteAuto = 0, kRouteFull = 1, kRouteHi16 = 2, kRouteFirst = 3;
+
+// a coded block's header after its first two bits, and its leading empty
+// planes; false on a malformed one
+template <class T, class R>
+__device__ __forceinline__ bool coded_head(R& r, uint32_t h, int minexp, int& emax, int& p, int& zlead) {
+  constexpr int P = FT<T>::P;
+  constexpr int EB = FT<T>::EBITS;
+  // unary escalation count, then the biased block exponent
+  int delta = (int)__builtin_ctz(~(h >> 2) | 0x40000000u);
+  if (3 + delta + EB <= 32) {
+    emax = (int)((h >> (3 + delta)) & ((1u << EB) - 1u)) - FT<T>::BIAS;
+    r.skip((uint32_t)(3 + delta + EB));
+  } else {
+    r.skip(2);
+    delta = 0;
+#pragma unroll 1
+    while (r.get(1)) {  // (rare: a long escalation; kept as a loop)
+      if (++delta > P) return false;
+    }
+    emax = (int)r.get((uint32_t)EB) - FT<T>::BIAS;
+  }
+  p = emax - minexp + kGuard;
+  p = (p < 0 ? 0 : (p > P ? P : p)) + delta;
+  if (emax < 2 - FT<T>::BIAS || p < 1 || p > P) return false;
+  // Leading empty planes: until a coefficient is significant, a plane
+  // without a new one is a single 0 (its negative group test), so the first
+  // zeros of the block's plane data are that many empty planes, skipped at once.
+  const int z0 = (int)__builtin_ctz(r.peek32() | 0x80000000u);
+  zlead = z0 < p ? z0 : p;
+  r.skip((uint32_t)zlead);
+  return true;
+}
+
 template <class T, int kRoute = kRouteAuto, class R>
 __device__ __forceinline__ bool decode_block_add(R& r, int minexp, T acc[64], const uint8_t* sq, bool rel) {
   typedef typename FT<T>::U U;
   constexpr int P = FT<T>::P;
-  constexpr int EB = FT<T>::EBITS;
   const uint32_t h = r.peek32();
   if (!(h & 1u)) {  // empty: x_i = 0 leaves x~ unchanged
     r.skip(1);
@@ -39,30 +76,8 @@ __device__ __forceinline__ bool decode_block_add(R& r, int minexp, T acc[64], co
     }
     return true;
   }
-  // unary escalation count, then the biased block exponent
-  int delta = (int)__builtin_ctz(~(h >> 2) | 0x40000000u);
-  int emax;
-  if (3 + delta + EB <= 32) {
-    emax = (int)((h >> (3 + delta)) & ((1u << EB) - 1u)) - FT<T>::BIAS;
-    r.skip((uint32_t)(3 + delta + EB));
-  } else {
-    r.skip(2);
-    delta = 0;
-#pragma unroll 1
-    while (r.get(1)) {  // (rare: a long escalation; kept as a loop)
-      if (++delta > P) return false;
-    }
-    emax = (int)r.get((uint32_t)EB) - FT<T>::BIAS;
-  }
-  int p = emax - minexp + kGuard;
-  p = (p < 0 ? 0 : (p > P ? P : p)) + delta;
-  if (emax < 2 - FT<T>::BIAS || p < 1 || p > P) return false;
-  // Leading empty planes: until a coefficient is significant, a plane
-  // without a new one is a single 0 (its negative group test), so the first
-  // zeros of the block's plane data are that many empty planes, skipped at once.
-  const int z0 = (int)__builtin_ctz(r.peek32() | 0x80000000u);
-  const int zlead = z0 < p ? z0 : p;
-  r.skip((uint32_t)zlead);
+  int emax, p, zlead;
+  if (!coded_head<T>(r, h, minexp, emax, p, zlead)) return false;
   if constexpr (sizeof(T) == 8 && kRoute == kRouteAuto) {
     // residual components whose coded planes all lie in the top ten bit
     // positions and keep every result normal: the lifting on the words' top
@@ -92,9 +107,9 @@ __device__ __forceinline__ bool decode_block_add(R& r, int minexp, T acc[64], co
       return true;
     }
   }
-  if constexpr (sizeof(T) == 4 && kRoute == kRouteHi16) {
+  if constexpr (kRoute == kRouteHi16) {
     // residual components (rel): the packed pairs straight from 4 or 8
-    // slots, else from the 32-bit words of 16
+    // slots, else from the 32-bit (high) words of 16
     v2s R2[32];
     const int np = p - zlead;
     if (__all(np <= 4)) {
@@ -102,18 +117,39 @@ __device__ __forceinline__ bool decode_block_add(R& r, int minexp, T acc[64], co
     } else if (__all(np <= 8)) {
       slots_hi16<8>(r, p, zlead, sq, R2);
     } else {
-      typename FT<T>::S c[64];
-      planes_slots<T, 16>(r, c, p, zlead, sq, rel);
+      int32_t c[64];
+      if constexpr (sizeof(T) == 4) planes_slots<T, 16>(r, c, p, zlead, sq, rel);
+      else coeffs_hi32<16>(r, p, zlead, c, sq, rel);
       pack_hi16(c, R2);
     }
     lift_dequant_add_hi16(R2, emax, acc);
     return true;
   }
-  typename FT<T>::S c[64], q[64];
-  planes_read<T>(r, c, p, zlead, sq, rel);
-  inverse_zy_ints<T>(c, q);
-  inverse_x<T>(q);
-  dequant_add(q, emax, acc);
+  if constexpr (kRoute != kRouteHi16) {
+    typename FT<T>::S c[64], q[64];
+    planes_read<T>(r, c, p, zlead, sq, rel);
+    inverse_zy_ints<T>(c, q);
+    inverse_x<T>(q);
+    dequant_add(q, emax, acc);
+  }
+  return true;
+}
+
+// a float64 store's first component on kRouteFirst: the block's words h and
+// exponent (zeros for an empty block), for the caller to turn into x~_1
+// outside the divergent part: x~ is not live while this decodes
+template <class R>
+__device__ __forceinline__ bool decode_first(R& r, int minexp, int32_t h[64], int& emax, const uint8_t* sq) {
+  const uint32_t hd = r.peek32();
+  if (!(hd & 1u)) {
+    r.skip(1);
+    return true;
+  }
+  int p, zlead;
+  if ((hd & 2u) || !coded_head<double>(r, hd, minexp, emax, p, zlead)) return false;
+  const int np = p - zlead;
+  if (__all(np <= 8)) words_hi32<8>(r, p, zlead, h, sq, false);
+  else words_hi32<16>(r, p, zlead, h, sq, false);
   return true;
 }
 
@@ -173,7 +209,7 @@ template <class T, bool kStaged, bool kBox = false, bool kFull = false, int kCod
 __device__ __forceinline__ bool decode_wave(const Geo& g, const uint8_t* const* s, const uint32_t* const* aux,
                                             const uint64_t* words, const int* minexp, const double* step, int ncomp,
                                             uint32_t relmask, const T* in, T* out, uint64_t w, const uint8_t* sq,
-                                            uint32_t* stage, const BoxArgs* box = nullptr) {
+                                            uint32_t* stage, const BoxArgs* box = nullptr, T* out2 = nullptr) {
   const uint32_t lane = threadIdx.x;
   const uint64_t blk = w * 64 + lane;
   bool active = blk < g.nblocks;
@@ -190,6 +226,13 @@ __device__ __forceinline__ bool decode_wave(const Geo& g, const uint8_t* const* 
   }
   const uint64_t chunk = blk / kChunkBlocks;
   T acc[64];
+  constexpr bool kHi64 = kHiRes && sizeof(T) == 8;  // (then in is null where component 0 is decoded)
+  int32_t h0[kHi64 ? 64 : 1];
+  int emax0 = 0;
+  if constexpr (kHi64) {
+#pragma unroll
+    for (int l = 0; l < 64; ++l) h0[l] = 0;
+  }
   if (in && active) {
     if constexpr (kBox) load_box(in, *box, bp, acc);
     else if constexpr (kFull) load_rows<T, 16>(in, g, opaque_pos(bp), 0, true, acc);
@@ -250,8 +293,11 @@ __device__ __forceinline__ bool decode_wave(const Geo& g, const uint8_t* const* 
             LBits r;
             r.init(stage + cur_base, start - s0 + (off >> 5), stop - s0, cur_cap);
             r.skip((uint32_t)(off & 31));
-            ok = decode_block_codec<T, kCodec, decltype(route)::value>(r, minexp[i], step[i], acc, sq,
-                                                                        (relmask >> i) & 1u) && !r.bad();
+            if constexpr (kHi64 && decltype(route)::value == kRouteFirst)
+              ok = decode_first(r, minexp[i], h0, emax0, sq) && !r.bad();
+            else
+              ok = decode_block_codec<T, kCodec, decltype(route)::value>(r, minexp[i], step[i], acc, sq,
+                                                                          (relmask >> i) & 1u) && !r.bad();
           }
         }
         if (i + 1 < ncomp && !pre) {  // staged after this component, into the whole buffer's first half or all of it
@@ -277,7 +323,13 @@ __device__ __forceinline__ bool decode_wave(const Geo& g, const uint8_t* const* 
       // the residual ones on the high-half route only
       int i = 0;
       if (ncomp > 0 && !(relmask & 1u)) {
-        component(0, std::integral_constant<int, kRouteFull>{});
+        if constexpr (kHi64) {
+          component(0, std::integral_constant<int, kRouteFirst>{});
+#pragma unroll
+          for (int l = 0; l < 64; ++l) acc[l] = __builtin_ldexp((double)h0[l], emax0 - 30);  // (+0) + x_1
+        } else {
+          component(0, std::integral_constant<int, kRouteFull>{});
+        }
         i = 1;
       }
       for (; i < ncomp; ++i) component(i, std::integral_constant<int, kRouteHi16>{});
@@ -317,16 +369,20 @@ __device__ __forceinline__ bool decode_wave(const Geo& g, const uint8_t* const* 
 #pragma unroll
       for (int r = 0; r < 16; ++r) store_row(out, g, bo, r, acc + 4 * r, true);
     } else {
-      store_block(out, g, block_pos(g, opaque(w) * 64 + lane), acc);
+      const BlockPos bo = block_pos(g, opaque(w) * 64 + lane);
+      store_block(out, g, bo, acc);
+      if (out2) store_block(out2, g, bo, acc);
     }
   }
   return ok || !active;
 }
 
-// kHiRes: the launch's residual components decode on the float32 high-half
-// route alone (the host has checked that every block of them qualifies)
+// kHiRes: the launch's residual components decode on the high-half route alone
+// and, in float64, its first component on kRouteFirst (every block of them
+// qualifies: the encoder and the index rebuild leave flags)
 template <class T, bool kStaged, bool kFull, int kCodec, bool kHiRes = false>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 3 : 1))) void k_decode(DecArgs<T> a) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 3 : kHiRes ? 2 : 1))) void k_decode(
+    DecArgs<T> a) {
   __shared__ uint8_t s_squeeze[256];
   __shared__ uint32_t s_stage[kStaged ? kStageWords + 3 : 1];
   squeeze_table(s_squeeze);
@@ -361,7 +417,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
 // many retrieval queries in one launch: wave w belongs to the query q with
 // wave_prefix[q] <= w < wave_prefix[q + 1]
 template <class T, bool kStaged, int kCodec, bool kHiRes = false>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 3 : 1))) void k_decode_queries(ServeArgs a) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 3 : kHiRes ? 2 : 1))) void k_decode_queries(
+    ServeArgs a) {
   __shared__ uint8_t s_squeeze[256];
   __shared__ uint32_t s_stage[kStaged ? kStageWords + 3 : 1];
   squeeze_table(s_squeeze);
@@ -391,7 +448,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
   if (!decode_wave<T, kStaged, false, false, kCodec, kHiRes>(
           g, (const uint8_t* const*)q.s, (const uint32_t* const*)q.aux, (const uint64_t*)q.words,
           (const int*)q.minexp, (const double*)q.step, q.ncomp, q.relmask, reinterpret_cast<const T*>(q.in),
-          reinterpret_cast<T*>(q.out), w - a.wave_prefix[lo], s_squeeze, s_stage))
+          reinterpret_cast<T*>(q.out), w - a.wave_prefix[lo], s_squeeze, s_stage, nullptr,
+          reinterpret_cast<T*>(q.out2)))
     atomicOr(a.status, 1u);
 }
 
@@ -403,7 +461,7 @@ void launch_decode_codec(const DecArgs<T>& a, uint64_t max_span, bool hires, hip
   const dim3 grid((uint32_t)wgs), wg(64);
   // every block full and every row aligned: the kernel without edge paths
   const bool full = a.g.nx % 4 == 0 && a.g.ny % 4 == 0 && a.g.nz % 4 == 0 && a.g.rows_aligned;
-  if constexpr (sizeof(T) == 4 && kCodec == 0) {
+  if constexpr (kCodec == 0) {
     if (hires && max_span <= kStageWords) {
       if (full) hipLaunchKernelGGL((k_decode<T, true, true, kCodec, true>), grid, wg, 0, s, a);
       else hipLaunchKernelGGL((k_decode<T, true, false, kCodec, true>), grid, wg, 0, s, a);
@@ -445,11 +503,9 @@ hipError_t launch_decode_queries(const ServeArgs& a, uint64_t max_span, int code
   if (a.nwaves == 0) return hipSuccess;
   const dim3 grid(a.nwaves), wg(64);
   const bool staged = max_span <= kStageWords;
-  if constexpr (sizeof(T) == 4) {
-    if (codec == 0 && hires && staged) {
-      hipLaunchKernelGGL((k_decode_queries<T, true, 0, true>), grid, wg, 0, s, a);
-      return hipGetLastError();
-    }
+  if (codec == 0 && hires && staged) {
+    hipLaunchKernelGGL((k_decode_queries<T, true, 0, true>), grid, wg, 0, s, a);
+    return hipGetLastError();
   }
   if (codec == 0) {
     if (staged) hipLaunchKernelGGL((k_decode_queries<T, true, 0>), grid, wg, 0, s, a);

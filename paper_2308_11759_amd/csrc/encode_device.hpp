@@ -640,13 +640,15 @@ __device__ __forceinline__ void encode_wave(const F& f, uint32_t wave, T* s_x, u
       const uint32_t nr = (uint32_t)__popcll(__ballot(mode == MODE_RAW));
       const uint32_t ns = (uint32_t)__popcll(__ballot(mode == MODE_CODED && delta > 0));
       const uint32_t nm = (uint32_t)__popcll(__ballot(miss));
-      const bool full = kCodec == 0 && sizeof(T) == 4 && __any(mode == MODE_CODED && !hi16_block<T>(p, emax));
+      const uint32_t rf = kCodec == 0 && mode == MODE_CODED ? route_flags<T>(p, emax) : 0u;
+      const bool not16 = __any(rf & kNotHi16), not32 = sizeof(T) == 8 && __any(rf & kNotHi32);
       const bool bad = __any(active && nonfinite);
       const double wm = wave_max_pos(err);
       if (lane == 0) {
         const uint64_t at = (uint64_t)i * job_waves(f) + wave;
         to_global(f.wave_linf)[at] = wm;
-        to_global(f.wave_stat)[at] = ne | (nr << 7) | (ns << 14) | (nm << 21) | (full ? kStatFull : 0u) |
+        to_global(f.wave_stat)[at] = ne | (nr << 7) | (ns << 14) | (nm << 21) | (not16 ? kStatNotHi16 : 0u) |
+                          (not32 ? kStatNotHi32 : 0u) |
                           (bad ? kStatNonfinite : 0u) | (over ? kStatOver : 0u);
         if (ncomp > 1) to_global(f.wave_start)[at] = start;
       }

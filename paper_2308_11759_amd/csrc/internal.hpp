@@ -48,7 +48,7 @@ struct pmc_store {
   std::vector<int> minexp;
   std::vector<uint64_t> bytes, offset, aux_offset, words, nempty, ncoded, nraw, nesc, nmiss;
   std::vector<uint64_t> max_span;  // largest payload words of a decode wave's four chunks
-  std::vector<uint64_t> full;      // nonzero: a coded block is outside the float32 high-half decode route
+  std::vector<uint64_t> full;      // decode route flags (kNotHi16, ...)
   const uint8_t* d_base = nullptr;  // caller-owned device memory holding the streams
 };
 
@@ -79,6 +79,17 @@ template <class A> void fill_decode_args(const pmc_store* s, int i0, int i1, A& 
     if (i > 0) a.relmask |= 1u << (i - i0);  // residual components
   }
   a.ncomp = i1 - i0;
+}
+
+// components [i0, i1) decode on the high-half route alone (see launch_decode);
+// in float64 a first component then starts from +0
+inline bool high_half(const pmc_store* s, int i0, int i1) {
+  if (s->codec != 0) return false;
+  for (int i = i0; i < i1; ++i) {
+    const uint64_t bad = i > 0 ? pmc::kNotHi16 : s->f.dtype == PMC_F32 ? 0u : pmc::kNotHi32 | pmc::kHasRaw;
+    if (s->full[i] & bad) return false;
+  }
+  return true;
 }
 
 inline hipEvent_t prof_event(pmc_ctx* c) {

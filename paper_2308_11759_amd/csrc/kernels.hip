@@ -32,16 +32,17 @@ __device__ __forceinline__ void aux_chunk(const AuxArgs& a, int comp, uint64_t c
   const uint64_t b0 = chunk * kChunkBlocks, b1 = min<uint64_t>(a.g.nblocks, b0 + kChunkBlocks);
   const int minexp = a.minexp[comp];
   uint32_t* const aux = a.aux[comp];
-  bool any_full = false;
+  uint32_t any = 0;
 #pragma unroll 1
   for (uint64_t blk = b0; blk < b1; ++blk) {
     aux[blk] = ok ? (uint32_t)r.consumed(from) : 0u;
-    bool full = false;
-    if (ok) ok = (kCodec == 0 ? block_skip<T>(r, minexp, sq, full) : pq_block_skip<T>(r)) && !r.bad();
-    any_full = any_full || full;
+    uint32_t flags = 0;
+    if (ok) ok = (kCodec == 0 ? block_skip<T>(r, minexp, sq, flags) : pq_block_skip<T>(r)) && !r.bad();
+    any |= flags;
   }
   if (!ok) atomicOr(a.status, 1u);
-  if (any_full && *(volatile unsigned long long*)(a.full + comp) == 0) atomicOr(a.full + comp, 1ull);
+  // flags, read first: most waves of such a component would raise them
+  if (any & ~(uint32_t)*(volatile unsigned long long*)(a.full + comp)) atomicOr(a.full + comp, (unsigned long long)any);
 }
 template <class T, int kCodec, int L>
 __global__ __launch_bounds__(64) void k_aux(AuxArgs a) {

@@ -17,6 +17,11 @@ enum : unsigned int {
   FLAG_STAGING = 8u     // a wave's staging slot was too small for every component
 };
 
+// what a component's blocks ask of the decode routes (CompMeta.full): a coded
+// block outside the high-half route; in float64 also one outside the high-word
+// route, and a raw block
+constexpr uint32_t kNotHi16 = 1u, kNotHi32 = 2u, kHasRaw = 4u;
+
 // per-component results kept on the device during compression
 struct CompMeta {
   unsigned long long linf_bits;  // max measured error, float64 bits (>= 0)
@@ -27,7 +32,7 @@ struct CompMeta {
   unsigned int flags;
   unsigned int pad;
   unsigned long long max_span;  // largest payload words of four consecutive chunks (one decode wave)
-  unsigned long long full;      // nonzero: some coded block is outside the float32 high-half decode route
+  unsigned long long full;      // decode route flags (kNotHi16, ...) of the component's blocks
   unsigned long long reserved[4];
 };
 static_assert(sizeof(CompMeta) == 128, "CompMeta layout");
@@ -49,9 +54,10 @@ static_assert(sizeof(TileRec) == 56, "TileRec layout");
 
 // one wave's record of one component (wave_stat): the counts of empty, raw,
 // escalated and missed blocks (7 bits each), then flags
-constexpr uint32_t kStatFull = 1u << 28;       // a coded block outside the float32 high-half decode route
+constexpr uint32_t kStatNotHi16 = 1u << 28;    // kNotHi16 of a block
 constexpr uint32_t kStatNonfinite = 1u << 29;  // NaN / Inf in the input
 constexpr uint32_t kStatOver = 1u << 30;       // the wave's slot was too small for this component
+constexpr uint32_t kStatNotHi32 = 1u << 31;    // kNotHi32 of a block
 
 // One field being compressed: components [comp0, comp1) in one launch.  The
 // encoder's waves (64 blocks, 4 chunks each) take their blocks through all of
@@ -123,6 +129,7 @@ struct QueryDev {
   int dtype;
   const void* in;
   void* out;
+  void* out2;  // NULL, or a second place for the result
   Geo g;
 };
 
@@ -143,7 +150,7 @@ struct AuxArgs {
   Geo g;
   uint32_t cap;  // words a wave's chunks can have
   unsigned int* status;  // set when a chunk fails to parse
-  unsigned long long* full;  // [component] set when a coded block is outside the float32 high-half route
+  unsigned long long* full;  // [component] decode route flags, raised
 };
 
 struct Item {  // (field, group): a wave of 64 blocks or a pack tile
@@ -172,9 +179,9 @@ template <class T> hipError_t launch_aux(AuxArgs a, int ncomp, uint64_t max_span
 // hires: as launch_decode's, for every query of the launch
 template <class T>
 hipError_t launch_decode_queries(const ServeArgs& a, uint64_t max_span, int codec, bool hires, hipStream_t s);
-// hires: every residual component of the launch (store index > 0) has no
-// block outside the float32 high-half route (CompMeta.full == 0), so the
-// decoder may run them on that route alone
+// hires: no residual component of the launch (store index > 0) has kNotHi16 and,
+// in float64, a first one neither kNotHi32 nor kHasRaw (and a.in is null then):
+// the decoder runs on those routes alone
 template <class T>
 hipError_t launch_decode(const DecArgs<T>& a, uint64_t max_span, int codec, bool hires, hipStream_t s);
 // components [0, a.ncomp) of the blocks meeting the box, written to a.out as the box alone

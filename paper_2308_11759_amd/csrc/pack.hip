@@ -86,7 +86,7 @@ __device__ __forceinline__ void take(const CFieldJob& f, int comp, uint64_t chun
     const uint32_t st = to_global(f.wave_stat)[at];
     s.counts = (unsigned long long)(st & 127u) | ((unsigned long long)((st >> 7) & 127u) << 16) |
                ((unsigned long long)((st >> 14) & 127u) << 32) | ((unsigned long long)((st >> 21) & 127u) << 48);
-    s.stat = st & (kStatFull | kStatNonfinite | kStatOver);
+    s.stat = st & (kStatNotHi16 | kStatNotHi32 | kStatNonfinite | kStatOver);
   }
 }
 // a component's totals over its tiles
@@ -116,7 +116,8 @@ __device__ __forceinline__ void write_meta(const CFieldJob& f, int comp, const T
   m.flags = (s.stat & kStatNonfinite ? FLAG_NONFINITE : 0u) | (s.stat & kStatOver ? FLAG_STAGING : 0u) |
             (offset + m.stream_bytes > f.region_cap ? FLAG_OVERFLOW : 0u) | (s.words > 0xFFFFFFFFull ? FLAG_INDEX : 0u);
   m.max_span = s.span;
-  m.full = s.stat & kStatFull ? 1ull : 0ull;
+  m.full = (s.stat & kStatNotHi16 ? kNotHi16 : 0u) | (s.stat & kStatNotHi32 ? kNotHi32 : 0u) |
+           (f.dtype == 2 && f.codec == 0 && s.nr ? kHasRaw : 0u);
   *(CompMeta*)(f.meta + comp) = m;
   if (f.host_meta) f.host_meta[comp] = m;
 }

@@ -88,7 +88,7 @@ struct CacheEntry {
   uint64_t off, bytes;
   uint64_t last_use;    // step counter
   uint64_t busy_step;   // last step that reads or writes the entry
-  uint64_t made_step;   // the step whose tail copy fills the entry
+  uint64_t made_step;   // the step that fills the entry
 };
 
 enum QState { Q_PENDING = 0, Q_RUNNING = 1, Q_DONE = 2, Q_RELEASED = 3 };
@@ -115,10 +115,19 @@ struct Step {
 };
 
 constexpr int kMaxInflight = 4;
-// (float32, float64) x (block transform, prediction), and float32 block
-// transform queries whose residual components all take the decoder's
-// high-half route (launched as their own instantiation)
-constexpr int kGroups = 5;
+// (float32, float64) x (block transform, prediction), and block transform
+// queries that take the decoder's high-half route alone (an instantiation of
+// its own), float32 and float64
+constexpr int kGroups = 6;
+// A step's table: the status word, then the queries of all groups, then their
+// wave prefixes, all packed, so that the upload is as large as the step (420 KB
+// per step went up when every group had max_batch entries of its own).  The
+// slot's size is what arenas have been sized for: five such groups.
+constexpr uint64_t kStatusBytes = 256;
+constexpr uint64_t slot_bytes_for(uint64_t max_batch) {
+  return ((5 * max_batch * (sizeof(QueryDev) - sizeof(void*)) + 5 * (max_batch + 1) * 4 + 256 + 255) & ~255ull) + 256;
+}
+static_assert(kStatusBytes + sizeof(QueryDev) + (1 + kGroups) * 4 <= slot_bytes_for(1), "a slot holds a step");
 
 }  // namespace
 
@@ -128,8 +137,8 @@ struct pmc_server {
   uint8_t* arena_base = nullptr;
   uint64_t arena_bytes = 0, budget = 0;
   int max_batch = 64;
-  // device tables: kMaxInflight slots of [kGroups x max_batch QueryDev | kGroups x (max_batch+1) prefixes |
-  // status]; a group per (element type, codec), each decoded by one launch
+  // device tables: kMaxInflight slots, a step each (see slot_bytes_for); a
+  // group of its queries is decoded by one launch
   uint64_t table_slot_bytes = 0;
   void* host_tables = nullptr;  // pinned staging, same layout
   bool slot_busy[kMaxInflight] = {false, false, false, false};
@@ -201,8 +210,7 @@ void retire(pmc_server* sv) {
     Step& st = sv->inflight.front();
     if (hipEventQuery(st.ev) != hipSuccess) break;
     const clk::time_point now = clk::now();
-    unsigned int* status = (unsigned int*)((uint8_t*)sv->host_tables + st.table_slot * sv->table_slot_bytes +
-                                           sv->table_slot_bytes - 256);
+    unsigned int* status = (unsigned int*)((uint8_t*)sv->host_tables + st.table_slot * sv->table_slot_bytes);
     const bool bad = *status != 0;
     for (uint64_t qi : st.queries) {
       Query& q = sv->queries[qi];
@@ -237,28 +245,12 @@ bool launch_step(pmc_server* sv) {
   const uint64_t step_id = ++sv->step_counter;
   uint8_t* htab = (uint8_t*)sv->host_tables + slot * sv->table_slot_bytes;
   uint8_t* dtab = sv->arena_base + slot * sv->table_slot_bytes;
-  QueryDev* hq[kGroups];
-  uint32_t* hpre[kGroups];
-  uint32_t nq[kGroups], nw[kGroups];
-  uint64_t span[kGroups];  // largest decode-wave span of the step's streams, per group
-  uint32_t* const pre0 = (uint32_t*)(htab + kGroups * sv->max_batch * sizeof(QueryDev));
-  for (int t = 0; t < kGroups; ++t) {
-    hq[t] = (QueryDev*)htab + t * sv->max_batch;
-    hpre[t] = pre0 + t * (sv->max_batch + 1);
-    hpre[t][0] = 0;
-    nq[t] = nw[t] = 0;
-    span[t] = 0;
-  }
+  std::vector<QueryDev> hq[kGroups];
+  uint64_t span[kGroups] = {};  // largest decode-wave span of the step's streams, per group
   uint32_t admitted = 0;
   Step st{};
   st.id = step_id;
   st.table_slot = slot;
-  struct CopyJob {
-    void* dst;
-    const void* src;
-    uint64_t bytes;
-  };
-  std::vector<CopyJob> copies;
   while (!sv->pending.empty() && admitted < (uint32_t)sv->max_batch) {
     const uint64_t qi = sv->pending.front();
     Query& q = sv->queries[qi];
@@ -281,11 +273,8 @@ bool launch_step(pmc_server* sv) {
     void* out = q.out ? q.out : (void*)(sv->arena_base + q.slot_off);
     const int ci = find_cache(sv, q.field, q.k, step_id);
     const int k0 = ci >= 0 ? sv->cache[ci].k : 0;
-    bool hires = s->f.dtype == PMC_F32 && s->codec == 0;
-    for (int c = k0; c < q.k; ++c)
-      if (c > 0 && s->full[c] != 0) hires = false;
-    const int t = hires ? 4 : (s->f.dtype == PMC_F32 ? 0 : 1) + 2 * s->codec;
-    QueryDev& d = hq[t][nq[t]];
+    const int t = (s->f.dtype == PMC_F32 ? 0 : 1) + (high_half(s, k0, q.k) ? 4 : 2 * s->codec);
+    QueryDev d;
     std::memset(&d, 0, sizeof(d));
     d.in = nullptr;
     if (ci >= 0) {
@@ -310,10 +299,6 @@ bool launch_step(pmc_server* sv) {
     d.dtype = s->f.dtype;
     d.out = out;
     d.g = s->g;
-    const uint32_t waves = (uint32_t)((s->g.nblocks + 63) / 64);
-    hpre[t][nq[t] + 1] = hpre[t][nq[t]] + waves;
-    nw[t] += waves;
-    nq[t]++;
     admitted++;
     // keep the new partial sum if it is not cached yet and there is room
     if (q.source != 2) {
@@ -323,9 +308,10 @@ bool launch_step(pmc_server* sv) {
       uint64_t off;
       if (!have && make_room(sv, fb) && sv->arena.alloc(fb, &off)) {
         sv->cache.push_back(CacheEntry{q.field, q.k, off, fb, step_id, step_id, step_id});
-        copies.push_back(CopyJob{sv->arena_base + off, out, fb});
+        d.out2 = sv->arena_base + off;  // written beside the result
       }
     }
+    hq[t].push_back(d);
     q.state = Q_RUNNING;
     q.step = step_id;
     st.queries.push_back(qi);
@@ -334,30 +320,39 @@ bool launch_step(pmc_server* sv) {
     --sv->step_counter;
     return false;
   }
-  unsigned int* hstatus = (unsigned int*)(htab + sv->table_slot_bytes - 256);
+  unsigned int* hstatus = (unsigned int*)htab;
   *hstatus = 0;
-  hipError_t e = hipMemcpyAsync(dtab, htab, sv->table_slot_bytes, hipMemcpyHostToDevice, sv->stream);
-  for (int t = 0; t < kGroups && e == hipSuccess; ++t) {
-    if (!nq[t]) continue;
-    ServeArgs a{};
-    a.q = (const QueryDev*)dtab + t * sv->max_batch;
-    a.wave_prefix = (const uint32_t*)(dtab + kGroups * sv->max_batch * sizeof(QueryDev)) + t * (sv->max_batch + 1);
-    a.nq = nq[t];
-    a.nwaves = nw[t];
-    a.status = (unsigned int*)(dtab + sv->table_slot_bytes - 256);
-    if (t == 4) {
-      e = launch_decode_queries<float>(a, span[t], 0, true, sv->stream);
-    } else {
-      const int codec = t / 2;
-      e = t % 2 == 0 ? launch_decode_queries<float>(a, span[t], codec, false, sv->stream)
-                     : launch_decode_queries<double>(a, span[t], codec, false, sv->stream);
+  const uint64_t pre_off = kStatusBytes + admitted * sizeof(QueryDev);
+  uint32_t* hpre = (uint32_t*)(htab + pre_off);
+  uint32_t nq0[kGroups], pre0[kGroups], nw[kGroups], nq = 0, np = 0;
+  for (int t = 0; t < kGroups; ++t) {
+    nq0[t] = nq;
+    pre0[t] = np;
+    nw[t] = 0;
+    hpre[np++] = 0;
+    for (const QueryDev& d : hq[t]) {
+      std::memcpy(htab + kStatusBytes + nq++ * sizeof(QueryDev), &d, sizeof(d));
+      nw[t] += (uint32_t)((d.g.nblocks + 63) / 64);
+      hpre[np++] = nw[t];
     }
   }
-  for (const CopyJob& c : copies)
-    if (e == hipSuccess) e = hipMemcpyAsync(c.dst, c.src, c.bytes, hipMemcpyDeviceToDevice, sv->stream);
+  hipError_t e = hipMemcpyAsync(dtab, htab, pre_off + np * 4, hipMemcpyHostToDevice, sv->stream);
+  for (int t = 0; t < kGroups && e == hipSuccess; ++t) {
+    if (hq[t].empty()) continue;
+    ServeArgs a{};
+    a.q = (const QueryDev*)(dtab + kStatusBytes) + nq0[t];
+    a.wave_prefix = (const uint32_t*)(dtab + pre_off) + pre0[t];
+    a.nq = (uint32_t)hq[t].size();
+    a.nwaves = nw[t];
+    a.status = (unsigned int*)dtab;
+    const bool hires = t >= 4;
+    const int codec = hires ? 0 : t / 2;
+    e = t % 2 == 0 ? launch_decode_queries<float>(a, span[t], codec, hires, sv->stream)
+                   : launch_decode_queries<double>(a, span[t], codec, hires, sv->stream);
+  }
   // the status word travels back into the pinned slot for retire()
   if (e == hipSuccess)
-    e = hipMemcpyAsync(hstatus, dtab + sv->table_slot_bytes - 256, 4, hipMemcpyDeviceToHost, sv->stream);
+    e = hipMemcpyAsync(hstatus, dtab, 4, hipMemcpyDeviceToHost, sv->stream);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&st.ev, hipEventDisableTiming);
   if (e == hipSuccess) e = hipEventRecord(st.ev, sv->stream);
   if (e != hipSuccess) {
@@ -420,7 +415,7 @@ pmc_status pmc_server_create(pmc_ctx* ctx, size_t hbm_budget, void* d_arena, siz
   pmc_server* sv = new pmc_server();
   sv->ctx = ctx;
   sv->max_batch = max_batch;
-  sv->table_slot_bytes = align256(kGroups * max_batch * sizeof(QueryDev) + kGroups * (max_batch + 1) * 4 + 256) + 256;
+  sv->table_slot_bytes = slot_bytes_for((uint64_t)max_batch);
   const uint64_t tables = kMaxInflight * sv->table_slot_bytes;
   if (arena_bytes < tables + 256) {
     delete sv;
