@@ -104,6 +104,11 @@ SIGNATURES = {
 }
 
 
+_new_bytes = ctypes.pythonapi.PyBytes_FromStringAndSize
+_new_bytes.restype = ctypes.py_object
+_new_bytes.argtypes = [_vp, ctypes.c_ssize_t]
+
+
 def load(path=LIB_PATH):
     """Load libpmc.so (raises if it was not built)."""
     global _lib
@@ -597,10 +602,13 @@ class Store:
     def serialize(self):
         used = ctypes.c_size_t()
         self.ctx._check(self.lib.pmc_store_serialize(self.ctx.handle, self.handle, None, 0, ctypes.byref(used)))
-        buf = ctypes.create_string_buffer(used.value)
-        self.ctx._check(self.lib.pmc_store_serialize(self.ctx.handle, self.handle, buf, used.value,
+        # straight into the memory of the bytes object that is returned (new,
+        # and not yet seen by anyone): no second buffer to clear and copy
+        blob = _new_bytes(None, used.value)
+        self.ctx._check(self.lib.pmc_store_serialize(self.ctx.handle, self.handle,
+                                                     ctypes.cast(ctypes.c_char_p(blob), _vp), used.value,
                                                      ctypes.byref(used)))
-        return buf.raw[:used.value]
+        return blob
 
     def free(self):
         if getattr(self, "handle", None):
