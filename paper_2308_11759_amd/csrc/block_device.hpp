@@ -175,6 +175,21 @@ __device__ __forceinline__ void store_box(T* __restrict__ f, const BoxArgs& bx, 
   }
 }
 
+// row r of a block into a box array
+template <class T>
+__device__ __forceinline__ void store_box_row(T* __restrict__ f, const BoxArgs& bx, const BlockPos& b, int r,
+                                              const T v[4]) {
+  const uint64_t nx = bx.hi[0] - bx.lo[0], ny = bx.hi[1] - bx.lo[1];
+  const uint64_t y = b.y0 + (r & 3), z = b.z0 + (r >> 2);
+  if (y < bx.lo[1] || y >= bx.hi[1] || z < bx.lo[2] || z >= bx.hi[2]) return;
+  T* row = f + nx * ((y - bx.lo[1]) + ny * (z - bx.lo[2]));
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const uint64_t x = b.x0 + k;
+    if (x >= bx.lo[0] && x < bx.hi[0]) row[x - bx.lo[0]] = v[k];
+  }
+}
+
 // load row r of a block (edge replication as in load_block); a null field
 // reads as +0
 template <class T>

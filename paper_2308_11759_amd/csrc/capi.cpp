@@ -620,10 +620,12 @@ static pmc_status decode_range(pmc_ctx* ctx, const pmc_store* s, int k0, int k1,
   // when the call checks it
   if (ctx->sync_check && (e = launch_fill64((unsigned long long*)status, 1, 0ull, ctx->stream)) != hipSuccess)
     return hipfail(ctx, e, "status init");
-  const int group = ctx->fused_decode ? kMaxDecode : 1;
+  const uint64_t waves = (s->g.nblocks + 63) / 64;
   const void* in = d_in;
-  for (int i0 = k0; i0 < k1; i0 += group) {
-    const int i1 = i0 + group < k1 ? i0 + group : k1;
+  for (int i0 = k0, i1; i0 < k1; i0 = i1) {
+    SplitArgs sp;
+    const SplitArgs* psp = ctx->fused_decode && split_plan(s, i0, k1, waves, &i1, &sp) ? &sp : nullptr;
+    if (!psp) i1 = std::min(i0 + (ctx->fused_decode ? kMaxDecode : 1), k1);
     uint64_t span = 0;
     for (int i = i0; i < i1; ++i) span = std::max(span, s->max_span[i]);
     const bool hires = high_half(s, i0, i1) && (i0 > 0 || !in);
@@ -635,7 +637,7 @@ static pmc_status decode_range(pmc_ctx* ctx, const pmc_store* s, int k0, int k1,
       a.g = s->g;
       a.status = status;
       ProfScope ps(ctx, s->codec == 0 ? "k_decode_f32" : "k_decode_pq_f32");
-      e = launch_decode<float>(a, span, s->codec, hires, ctx->stream);
+      e = launch_decode<float>(a, span, s->codec, hires, psp, ctx->stream);
     } else {
       DecArgs<double> a{};
       fill_decode_args(s, i0, i1, a);
@@ -644,7 +646,7 @@ static pmc_status decode_range(pmc_ctx* ctx, const pmc_store* s, int k0, int k1,
       a.g = s->g;
       a.status = status;
       ProfScope ps(ctx, s->codec == 0 ? "k_decode_f64" : "k_decode_pq_f64");
-      e = launch_decode<double>(a, span, s->codec, hires, ctx->stream);
+      e = launch_decode<double>(a, span, s->codec, hires, psp, ctx->stream);
     }
     if (e != hipSuccess) return hipfail(ctx, e, "decode");
     in = d_out;
@@ -681,11 +683,15 @@ pmc_status pmc_retrieve_box(pmc_ctx* ctx, const pmc_store* s, int k, const uint6
     b.bhi[a] = (hi[a] + 3) / 4;
   }
   b.waves_per_row = (uint32_t)((b.bhi[0] - b.blo[0] + 63) / 64 + 1);  // a row of blocks meets at most this many waves
+  const uint64_t waves = (b.bhi[0] - b.blo[0] + 63) / 64 * (b.bhi[1] - b.blo[1]) * (b.bhi[2] - b.blo[2]);
   const void* in = nullptr;
-  for (int i0 = 0; i0 < k; i0 += kMaxDecode) {
-    const int i1 = i0 + kMaxDecode < k ? i0 + kMaxDecode : k;
+  for (int i0 = 0, i1; i0 < k; i0 = i1) {
+    SplitArgs sp;
+    const SplitArgs* psp = split_plan(s, i0, k, waves, &i1, &sp) ? &sp : nullptr;
+    if (!psp) i1 = std::min(i0 + kMaxDecode, k);
     uint64_t span = 0;
     for (int i = i0; i < i1; ++i) span = std::max(span, s->max_span[i]);
+    const bool hires = high_half(s, i0, i1);
     if (s->f.dtype == PMC_F32) {
       DecArgs<float> a{};
       fill_decode_args(s, i0, i1, a);
@@ -693,7 +699,7 @@ pmc_status pmc_retrieve_box(pmc_ctx* ctx, const pmc_store* s, int k, const uint6
       a.out = (float*)d_out;
       a.g = s->g;
       a.status = status;
-      e = launch_decode_box<float>(a, b, span, s->codec, ctx->stream);
+      e = launch_decode_box<float>(a, b, span, s->codec, hires, psp, ctx->stream);
     } else {
       DecArgs<double> a{};
       fill_decode_args(s, i0, i1, a);
@@ -701,7 +707,7 @@ pmc_status pmc_retrieve_box(pmc_ctx* ctx, const pmc_store* s, int k, const uint6
       a.out = (double*)d_out;
       a.g = s->g;
       a.status = status;
-      e = launch_decode_box<double>(a, b, span, s->codec, ctx->stream);
+      e = launch_decode_box<double>(a, b, span, s->codec, hires, psp, ctx->stream);
     }
     if (e != hipSuccess) return hipfail(ctx, e, "decode");
     in = d_out;

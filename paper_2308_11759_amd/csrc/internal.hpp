@@ -92,6 +92,53 @@ inline bool high_half(const pmc_store* s, int i0, int i1) {
   return true;
 }
 
+// The next launch [i0, i1) of a retrieval of components [i0, k), and its
+// staging plan if it decodes `waves` waves of blocks with one wave per
+// component (k_decode_split); false where one wave decodes all of them.
+//
+// A launch takes up to eight components (float64 off the high-half routes
+// four: 850 spills at the 256 registers of eight), launches of about the same
+// size and as few as there can be, and asks for at most 64 KB of LDS per
+// workgroup.  It is taken where few rounds of workgroups cover the field: one
+// wave costs about 5 us per component while the chip is not full, a round of
+// workgroups 13 (float64 16).  Measured (us, one wave / split): float32, 8
+// components: 64 waves 44.9 / 17.4, 512 (2 rounds) 47.1 / 30.6, 729 (3) 46.6 /
+// 42.2, 1000 (4) 46.6 / 53.5; 6: 512 (2) 43.8 / 31.6, 729 (3) 43.5 / 43.7; 4:
+// 1000 (2) 32.2 / 31.1; 3: 1000 (1) 27.3 / 25.5; 2: 216 (1) 20.1 / 18.2, 1954
+// (2) 29.5 / 39.6.  float64, 8: 64 waves 44.1 / 22.2, 512 (2) 46.9 / 40.5, 729
+// (3) 49.6 / 57.4; off the high-half routes, 4: 216 (1) 31.5 / 18.8; 6 in two
+// launches: 64 41.3 / 36.6, 343 (2) 42.4 / 66.5.
+inline bool split_plan(const pmc_store* s, int i0, int k, uint64_t waves, int* i1, pmc::SplitArgs* sp) {
+  const bool f32 = s->f.dtype == PMC_F32;
+  int most = pmc::kMaxSplit, n = 0, launches = 0;
+  bool hires = false;
+  for (;;) {
+    launches = (k - i0 + most - 1) / most;
+    n = (k - i0 + launches - 1) / launches;
+    hires = high_half(s, i0, i0 + n);
+    if (f32 || hires || most == pmc::kMaxSplit64) break;
+    most = pmc::kMaxSplit64;
+  }
+  if (n < 2) return false;
+  uint64_t words = 0;
+  for (int j = 0; j < n; ++j) {
+    const uint64_t cap = (std::max<uint64_t>(s->max_span[i0 + j], 1) + 63) / 64 * 64;  // copies write whole 64-word rows
+    if (cap > 16384) return false;
+    sp->base[j] = (uint32_t)words;
+    sp->cap[j] = (uint32_t)cap;
+    words += cap + 3;  // the reader's look-ahead
+  }
+  const uint64_t lds = std::max(words * 4, (uint64_t)n * 4096);  // the words, then 4 KB of rows per component
+  if (lds > 65536 - 512) return false;
+  const uint64_t slots = f32 ? 12 : hires ? 8 : 4;  // waves a CU's registers hold
+  const uint64_t resident = 256 * std::min(slots / n, 163840 / (lds + 512));
+  const uint64_t rounds = (waves + resident - 1) / resident;
+  if ((f32 ? 13 : 16) * rounds * launches > 5 * (uint64_t)(k - i0) + 6) return false;
+  sp->lds_bytes = (uint32_t)lds;
+  *i1 = i0 + n;
+  return true;
+}
+
 inline hipEvent_t prof_event(pmc_ctx* c) {
   if (!c->prof_pool.empty()) {
     hipEvent_t e = c->prof_pool.back();

@@ -108,6 +108,13 @@ template <class T> struct DecArgs {
 // a box [lo, hi) of the field (value coordinates x, y, z) for region
 // retrieval: blo/bhi are its block ranges; the output is the box alone, dense,
 // x fastest.  Work: one workgroup per (block row of the box, wave of that row)
+// a launch with one wave per component: where each component's words are
+// staged in the workgroup's LDS (word offset, and words it holds)
+constexpr int kMaxSplit = 8, kMaxSplit64 = 4;  // (4: float64 that is not hires)
+struct SplitArgs {  // (launch_decode, launch_decode_box: null for one wave over all components)
+  uint32_t base[kMaxSplit], cap[kMaxSplit];
+  uint32_t lds_bytes;
+};
 struct BoxArgs {
   uint64_t lo[3], hi[3];
   uint64_t blo[3], bhi[3];
@@ -183,10 +190,12 @@ hipError_t launch_decode_queries(const ServeArgs& a, uint64_t max_span, int code
 // in float64, a first one neither kNotHi32 nor kHasRaw (and a.in is null then):
 // the decoder runs on those routes alone
 template <class T>
-hipError_t launch_decode(const DecArgs<T>& a, uint64_t max_span, int codec, bool hires, hipStream_t s);
+hipError_t launch_decode(const DecArgs<T>& a, uint64_t max_span, int codec, bool hires, const SplitArgs* split,
+                         hipStream_t s);
 // components [0, a.ncomp) of the blocks meeting the box, written to a.out as the box alone
 template <class T>
-hipError_t launch_decode_box(const DecArgs<T>& a, const BoxArgs& b, uint64_t max_span, int codec, hipStream_t s);
+hipError_t launch_decode_box(const DecArgs<T>& a, const BoxArgs& b, uint64_t max_span, int codec, bool hires,
+                             const SplitArgs* split, hipStream_t s);
 uint64_t stage_words();  // capacity of the decoder's LDS staging buffer, in words
 // min / max / non-finite count of n samples: one partial of kRangeWords words
 // per workgroup at out; range_groups: how many workgroups suit n, at most
