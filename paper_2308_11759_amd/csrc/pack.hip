@@ -33,6 +33,9 @@ constexpr int kTileWaves = kPackTile / 4;  // encoder waves of a tile
 // at most 16 loads per lane and component, where two more launches cost about
 // 10 us.
 constexpr uint64_t kDirectChunks = kPackThreads;
+// ... and several workgroups to a tile, each moving a part of its spans: one
+// per wave, where 16 waves took four each (64^3 float64, 4 components: 18 us).
+constexpr uint32_t kDirectParts = kTileWaves / (kPackThreads / 64);
 
 struct Sums {
   unsigned long long words;
@@ -214,7 +217,10 @@ __device__ __forceinline__ void pack_heads(const CFieldJob& f, int comp) {
   }
 }
 
-template <bool kDirect> __device__ __forceinline__ void pack_tile(const CFieldJob& f, int comp, uint64_t tile) {
+// part of parts: the workgroup's share of the tile's spans
+template <bool kDirect>
+__device__ __forceinline__ void pack_tile(const CFieldJob& f, int comp, uint64_t tile, uint32_t part = 0,
+                                          uint32_t parts = 1) {
   __shared__ Sums sh[kPackThreads / 64];
   __shared__ unsigned long long s_words[kMaxComps];
   __shared__ uint32_t s_pre[kPackTile + 1];  // words before each chunk of the tile
@@ -242,7 +248,7 @@ template <bool kDirect> __device__ __forceinline__ void pack_tile(const CFieldJo
     offset = stream_offset(f, comp, s_words);
     const unsigned long long end = offset + kHeaderBytes + 4ull * nchunks + 4ull * words;
     flags = (s.stat & kStatOver) || end > f.region_cap || words > 0xFFFFFFFFull;
-    if (tile == 0 && t == 0) {
+    if (tile == 0 && part == 0 && t == 0) {
       Totals m = {};
       m.words = words;
       add_counts(m, s);
@@ -281,12 +287,13 @@ template <bool kDirect> __device__ __forceinline__ void pack_tile(const CFieldJo
     for (uint32_t q = 0; q < wv; ++q) inc += s_wave[q];
     s_pre[t + 1] = inc;
     if (t == 0) s_pre[0] = 0;
-    if (chunk < nchunks) index[chunk] = (uint32_t)before + inc - w;
+    if (part == 0 && chunk < nchunks) index[chunk] = (uint32_t)before + inc - w;
   }
   __syncthreads();
 
   // the spans: one wave moves one encoder wave's words at a time
-  for (uint32_t q = wv; q < (uint32_t)kTileWaves && wave0 + q < job_waves(f); q += kPackThreads / 64) {
+  for (uint32_t q = wv + part * (kPackThreads / 64); q < (uint32_t)kTileWaves && wave0 + q < job_waves(f);
+       q += parts * (kPackThreads / 64)) {
     const uint32_t o = s_pre[4 * q], span = s_pre[4 * q + 4] - o, start = s_start[q];
     const uint64_t wave = wave0 + q;
     const gptr<const uint32_t> src = to_global((const uint32_t*)f.staging) + (wave * f.slot_words + start);
@@ -308,7 +315,7 @@ template <bool kDirect> __device__ __forceinline__ void pack_tile(const CFieldJo
     if (lane < span - 4 * n16) dst[4 * n16 + lane] = src[4 * n16 + lane];
   }
 
-  if (tile == 0 && t < 16) {
+  if (tile == 0 && part == 0 && t < 16) {
     const uint64_t taub = (uint64_t)__double_as_longlong(f.tau[comp]);
     uint32_t v = 0;
     switch (t) {
@@ -347,7 +354,7 @@ __global__ __launch_bounds__(kPackThreads) void k_pack_heads(FieldJob) {
 }
 template <bool kDirect> __global__ __launch_bounds__(kPackThreads) void k_pack(FieldJob) {
   const CFieldJob& f = arg_job();
-  pack_tile<kDirect>(f, f.comp0 + (int)blockIdx.y, blockIdx.x);
+  pack_tile<kDirect>(f, f.comp0 + (int)blockIdx.y, blockIdx.x, blockIdx.z, kDirect ? kDirectParts : 1u);
 }
 __global__ __launch_bounds__(kSumThreads) void k_bpack_sums(BatchArgs b) {
   const Item it = b.items[blockIdx.x];
@@ -371,7 +378,7 @@ hipError_t launch_pack(const FieldJob& f, hipStream_t s) {
   const uint32_t comps = (uint32_t)(f.comp1 - f.comp0);
   const dim3 tiles(job_tiles(f), comps), wg(kPackThreads);
   if (f.g.nchunks <= kDirectChunks) {
-    hipLaunchKernelGGL(k_pack<true>, tiles, wg, 0, s, f);
+    hipLaunchKernelGGL(k_pack<true>, dim3(tiles.x, tiles.y, kDirectParts), wg, 0, s, f);
   } else {
     hipLaunchKernelGGL(k_pack_sums, tiles, dim3(kSumThreads), 0, s, f);
     hipLaunchKernelGGL(k_pack_heads, dim3(comps), wg, 0, s, f);
