@@ -72,21 +72,31 @@ __device__ __forceinline__ uint64_t row_step(const Geo& g, int r) {
   return g.nx * (uint64_t)(r & 3) + g.nx * g.ny * (uint64_t)(r >> 2);
 }
 
+// Row pieces are 16-byte accesses at any sample: rows whose length is no
+// multiple of 16 bytes take them too.  Four 4-byte accesses with a 16-byte
+// stride between lanes had cost four times the requests: 251x203x181 float32
+// refined component by component, six calls, 173 us, now 126.  (The encoder,
+// which puts such rows into LDS once for all components, gained nothing.)
+typedef float any_f4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef double any_d2 __attribute__((ext_vector_type(2), aligned(8)));
+template <class T> __device__ __forceinline__ void load_row16(const T* row, T v[4]) {
+  if constexpr (sizeof(T) == 4) {
+    const any_f4 q = *reinterpret_cast<const any_f4*>(row);
+    v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
+  } else {
+    const any_d2 q0 = *reinterpret_cast<const any_d2*>(row);
+    const any_d2 q1 = *reinterpret_cast<const any_d2*>(row + 2);
+    v[0] = q0.x; v[1] = q0.y; v[2] = q1.x; v[3] = q1.y;
+  }
+}
+
 template <class T>
 __device__ __forceinline__ void load_block(const T* __restrict__ f, const Geo& g, const BlockPos& b, T v[64]) {
-  const bool vec = b.vx == 4 && g.rows_aligned;
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     const T* row = row_ptr(f, g, b, r);
-    if (vec) {
-      if constexpr (sizeof(T) == 4) {
-        float4 q = *reinterpret_cast<const float4*>(row);
-        v[4 * r] = q.x; v[4 * r + 1] = q.y; v[4 * r + 2] = q.z; v[4 * r + 3] = q.w;
-      } else {
-        double2 q0 = *reinterpret_cast<const double2*>(row);
-        double2 q1 = *reinterpret_cast<const double2*>(row + 2);
-        v[4 * r] = q0.x; v[4 * r + 1] = q0.y; v[4 * r + 2] = q1.x; v[4 * r + 3] = q1.y;
-      }
+    if (b.vx == 4) {
+      load_row16(row, v + 4 * r);
     } else {
       const uint32_t m = b.vx - 1;
       v[4 * r] = row[0];
@@ -107,27 +117,25 @@ typedef uint32_t nt_u4 __attribute__((ext_vector_type(4)));
 template <class T>
 __device__ __forceinline__ void store_row16_nt(T* row, T a, T b, T c, T d) {
   if constexpr (sizeof(T) == 4) {
-    __builtin_nontemporal_store(nt_f4{a, b, c, d}, reinterpret_cast<nt_f4*>(row));
+    __builtin_nontemporal_store(any_f4{a, b, c, d}, reinterpret_cast<any_f4*>(row));
   } else {
-    __builtin_nontemporal_store(nt_d2{a, b}, reinterpret_cast<nt_d2*>(row));
-    __builtin_nontemporal_store(nt_d2{c, d}, reinterpret_cast<nt_d2*>(row + 2));
+    __builtin_nontemporal_store(any_d2{a, b}, reinterpret_cast<any_d2*>(row));
+    __builtin_nontemporal_store(any_d2{c, d}, reinterpret_cast<any_d2*>(row + 2));
   }
 }
 
 template <class T>
 __device__ __forceinline__ void store_block(T* __restrict__ f, const Geo& g, const BlockPos& b, const T v[64]) {
-  const bool vec = b.vx == 4 && g.rows_aligned;
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     if ((uint32_t)(r & 3) >= b.vy || (uint32_t)(r >> 2) >= b.vz) continue;
     T* row = const_cast<T*>(row_ptr((const T*)f, g, b, r));
-    if (vec) {
+    if (b.vx == 4) {
       store_row16_nt(row, v[4 * r], v[4 * r + 1], v[4 * r + 2], v[4 * r + 3]);
     } else {
       row[0] = v[4 * r];
       if (b.vx > 1) row[1] = v[4 * r + 1];
       if (b.vx > 2) row[2] = v[4 * r + 2];
-      if (b.vx > 3) row[3] = v[4 * r + 3];
     }
   }
 }
@@ -140,13 +148,12 @@ __device__ __forceinline__ void store_row(T* __restrict__ f, const Geo& g, const
                                           bool wfull = false) {
   if (!wfull && ((uint32_t)(r & 3) >= b.vy || (uint32_t)(r >> 2) >= b.vz)) return;
   T* row = wfull ? block_base(f, g, b) + row_step(g, r) : const_cast<T*>(row_ptr((const T*)f, g, b, r));
-  if (wfull || (b.vx == 4 && g.rows_aligned)) {
+  if (wfull || b.vx == 4) {
     store_row16_nt(row, v[0], v[1], v[2], v[3]);
   } else {
     row[0] = v[0];
     if (b.vx > 1) row[1] = v[1];
     if (b.vx > 2) row[2] = v[2];
-    if (b.vx > 3) row[3] = v[3];
   }
 }
 
@@ -165,29 +172,26 @@ __device__ __forceinline__ void load_box(const T* __restrict__ f, const BoxArgs&
   }
 }
 template <class T>
-__device__ __forceinline__ void store_box(T* __restrict__ f, const BoxArgs& bx, const BlockPos& b, const T v[64]) {
-  const uint64_t nx = bx.hi[0] - bx.lo[0], ny = bx.hi[1] - bx.lo[1];
-#pragma unroll
-  for (int l = 0; l < 64; ++l) {
-    const uint64_t x = b.x0 + (l & 3), y = b.y0 + ((l >> 2) & 3), z = b.z0 + (l >> 4);
-    if (x >= bx.lo[0] && x < bx.hi[0] && y >= bx.lo[1] && y < bx.hi[1] && z >= bx.lo[2] && z < bx.hi[2])
-      f[(x - bx.lo[0]) + nx * ((y - bx.lo[1]) + ny * (z - bx.lo[2]))] = v[l];
-  }
-}
-
-// row r of a block into a box array
-template <class T>
 __device__ __forceinline__ void store_box_row(T* __restrict__ f, const BoxArgs& bx, const BlockPos& b, int r,
                                               const T v[4]) {
   const uint64_t nx = bx.hi[0] - bx.lo[0], ny = bx.hi[1] - bx.lo[1];
   const uint64_t y = b.y0 + (r & 3), z = b.z0 + (r >> 2);
   if (y < bx.lo[1] || y >= bx.hi[1] || z < bx.lo[2] || z >= bx.hi[2]) return;
   T* row = f + nx * ((y - bx.lo[1]) + ny * (z - bx.lo[2]));
+  if (b.x0 >= bx.lo[0] && b.x0 + 4 <= bx.hi[0]) {
+    store_row16_nt(row + (b.x0 - bx.lo[0]), v[0], v[1], v[2], v[3]);
+  } else {
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const uint64_t x = b.x0 + k;
-    if (x >= bx.lo[0] && x < bx.hi[0]) row[x - bx.lo[0]] = v[k];
+    for (int k = 0; k < 4; ++k) {
+      const uint64_t x = b.x0 + k;
+      if (x >= bx.lo[0] && x < bx.hi[0]) row[x - bx.lo[0]] = v[k];
+    }
   }
+}
+template <class T>
+__device__ __forceinline__ void store_box(T* __restrict__ f, const BoxArgs& bx, const BlockPos& b, const T v[64]) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r) store_box_row(f, bx, b, r, v + 4 * r);
 }
 
 // load row r of a block (edge replication as in load_block); a null field
@@ -200,15 +204,8 @@ __device__ __forceinline__ void load_row(const T* f, const Geo& g, const BlockPo
     return;
   }
   const T* row = row_ptr(f, g, b, r);
-  if (b.vx == 4 && g.rows_aligned) {
-    if constexpr (sizeof(T) == 4) {
-      float4 q = *reinterpret_cast<const float4*>(row);
-      v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
-    } else {
-      double2 q0 = *reinterpret_cast<const double2*>(row);
-      double2 q1 = *reinterpret_cast<const double2*>(row + 2);
-      v[0] = q0.x; v[1] = q0.y; v[2] = q1.x; v[3] = q1.y;
-    }
+  if (b.vx == 4) {
+    load_row16(row, v);
   } else {
     const uint32_t m = b.vx - 1;
     v[0] = row[0];
@@ -236,14 +233,7 @@ __device__ __forceinline__ void load_rows(const T* f, const Geo& g, const BlockP
 #pragma unroll
     for (int k = 0; k < R; ++k) {
       const T* row = base + row_step(g, r0 + k);
-      if constexpr (sizeof(T) == 4) {
-        const float4 q = *reinterpret_cast<const float4*>(row);
-        v[4 * k] = q.x; v[4 * k + 1] = q.y; v[4 * k + 2] = q.z; v[4 * k + 3] = q.w;
-      } else {
-        const double2 q0 = *reinterpret_cast<const double2*>(row);
-        const double2 q1 = *reinterpret_cast<const double2*>(row + 2);
-        v[4 * k] = q0.x; v[4 * k + 1] = q0.y; v[4 * k + 2] = q1.x; v[4 * k + 3] = q1.y;
-      }
+      load_row16(row, v + 4 * k);
     }
   } else {
 #pragma unroll
