@@ -682,8 +682,17 @@ pmc_status pmc_retrieve_box(pmc_ctx* ctx, const pmc_store* s, int k, const uint6
     b.blo[a] = lo[a] / 4;
     b.bhi[a] = (hi[a] + 3) / 4;
   }
-  b.waves_per_row = (uint32_t)((b.bhi[0] - b.blo[0] + 63) / 64 + 1);  // a row of blocks meets at most this many waves
-  const uint64_t waves = (b.bhi[0] - b.blo[0] + 63) / 64 * (b.bhi[1] - b.blo[1]) * (b.bhi[2] - b.blo[2]);
+  // a row of blocks meets at most this many waves; where the field's rows
+  // start on a wave's first block, as many as the first row does
+  const uint64_t nbx = b.bhi[0] - b.blo[0];
+  const bool whole = s->g.nbx % 64 == 0;
+  b.waves_per_row = (uint32_t)(whole ? (b.blo[0] % 64 + nbx + 63) / 64 : (nbx + 63) / 64 + 1);
+  // for the split's cost rule: the waves launched, those that find no block
+  // (all but about (63 + nbx) / 64 of a row) at half (300^3, 8 components, a
+  // 100^3 box: 625 rows, one wave per component 76 us, one for all 70; 64^3:
+  // 256 rows, 35 / 64; 256^3, 100^3: 48 / 53)
+  const uint64_t rows = (b.bhi[1] - b.blo[1]) * (b.bhi[2] - b.blo[2]);
+  const uint64_t waves = whole ? rows * b.waves_per_row : rows * (63 + nbx + 64ull * b.waves_per_row) / 128;
   const void* in = nullptr;
   for (int i0 = 0, i1; i0 < k; i0 = i1) {
     SplitArgs sp;
