@@ -255,9 +255,10 @@ void pmc_store_free(pmc_store* s);
 
 /* ---- batches: many fields of uneven size and mixed type ---------------
  * Alg. 1 for nf fields at once.  All components of all fields run as one
- * captured HIP graph, replayed on every pmc_batch_compress: per component a
- * persistent encode kernel per element type walks a list of (field, 64-block
- * group) items, then a segmented chunk scan and a batched pack run.  The
+ * captured HIP graph, replayed on every pmc_batch_compress: a persistent
+ * encode kernel per element type walks a list of (field, 64-block group)
+ * items, each through all its components, then three pack launches lay out
+ * and write every stream of every field.  The
  * schedule (persistent grid = grid_mult x compute units; item order 0 =
  * field-major, 1 = interleaved across fields, 2 = largest field first) never
  * changes the output bytes.  n[i] components for field i with tolerances
