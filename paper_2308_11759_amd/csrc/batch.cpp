@@ -36,10 +36,10 @@ struct pmc_batch {
   // stream regions (byte offsets into d_streams)
   std::vector<uint64_t> region_off, region_cap;
   uint64_t streams_total = 0;
-  // items: [encode f32 | encode f64 | pack tiles]
-  std::vector<Item> items;
+  // what goes up for a call: the job table and, as far behind it as in the
+  // workspace, the items [encode f32 | encode f64 | pack tiles]
+  std::vector<uint8_t> upload;
   uint32_t n32 = 0, n64 = 0, ntiles = 0;
-  uint64_t items_cap = 0;
   // schedule
   int grid_mult = 4, order = 0;
   int cus = 256;
@@ -50,42 +50,43 @@ struct pmc_batch {
   const void* g_ws = nullptr;
   const void* g_streams = nullptr;
   int g_grid = -1, g_order = -1;
-  bool items_uploaded = false;
-  std::vector<int> uploaded_order;
 };
 
 namespace {
 
 const char* kOrderName[3] = {"field-major", "interleaved", "largest-first"};
 
-// wave items of one element type in the requested order
+// the items in the requested order, put behind the job table of the upload
 void build_items(pmc_batch* b) {
-  b->items.clear();
+  std::vector<Item> items;
   for (int dt = 1; dt <= 2; ++dt) {
     std::vector<int> fl;
     for (int i = 0; i < b->nf; ++i)
       if (b->f[i].dtype == dt) fl.push_back(i);
     if (b->order == 2)
       std::stable_sort(fl.begin(), fl.end(), [&](int a, int c) { return b->g[a].nblocks > b->g[c].nblocks; });
-    size_t before = b->items.size();
+    size_t before = items.size();
     if (b->order == 1) {
       uint64_t maxw = 0;
       for (int i : fl) maxw = std::max<uint64_t>(maxw, (b->g[i].nblocks + 63) / 64);
       for (uint64_t w = 0; w < maxw; ++w)
         for (int i : fl)
-          if (w < (b->g[i].nblocks + 63) / 64) b->items.push_back(Item{(uint32_t)i, (uint32_t)w});
+          if (w < (b->g[i].nblocks + 63) / 64) items.push_back(Item{(uint32_t)i, (uint32_t)w});
     } else {
       for (int i : fl)
-        for (uint64_t w = 0; w < (b->g[i].nblocks + 63) / 64; ++w) b->items.push_back(Item{(uint32_t)i, (uint32_t)w});
+        for (uint64_t w = 0; w < (b->g[i].nblocks + 63) / 64; ++w) items.push_back(Item{(uint32_t)i, (uint32_t)w});
     }
-    (dt == 1 ? b->n32 : b->n64) = (uint32_t)(b->items.size() - before);
+    (dt == 1 ? b->n32 : b->n64) = (uint32_t)(items.size() - before);
   }
   b->ntiles = 0;
   for (int i = 0; i < b->nf; ++i) {
     const uint64_t t = (b->g[i].nchunks + kPackTile - 1) / kPackTile;
-    for (uint64_t j = 0; j < t; ++j) b->items.push_back(Item{(uint32_t)i, (uint32_t)j});
+    for (uint64_t j = 0; j < t; ++j) items.push_back(Item{(uint32_t)i, (uint32_t)j});
     b->ntiles += (uint32_t)t;
   }
+  const uint64_t table = b->off_items - b->off_table, bytes = items.size() * sizeof(Item);
+  b->upload.resize(table + bytes);
+  std::memcpy(b->upload.data() + table, items.data(), bytes);
 }
 
 void drop_graph(pmc_batch* b) {
@@ -197,19 +198,18 @@ pmc_status pmc_batch_plan(pmc_ctx* ctx, int nf, const pmc_field* fields, const i
   }
   b->off_table = ws;
   ws += align256((uint64_t)nf * sizeof(FieldJob));
+  b->off_items = ws;
+  ws += align256(room * sizeof(Item));  // at least the items: a pack tile takes the place of 64 chunk quads
   b->off_meta = ws;
   ws += align256(nmeta * sizeof(CompMeta));
-  b->off_items = ws;
+  b->ws_total = ws;
+  b->streams_total = reg;
   int gm = 4, od = 0;
   if (tune_lookup(b, &gm, &od)) {
     b->grid_mult = gm;
     b->order = od;
   }
   build_items(b);
-  b->items_cap = room;  // at least items.size(): a pack tile takes the place of 64 chunk quads
-  ws += align256(b->items_cap * sizeof(Item));
-  b->ws_total = ws;
-  b->streams_total = reg;
   if (hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking) != hipSuccess) {
     delete b;
     return fail(ctx, PMC_E_DEVICE, "stream creation failed");
@@ -231,7 +231,6 @@ pmc_status pmc_batch_schedule(pmc_batch* b, int grid_mult, int order) {
     b->grid_mult = grid_mult;
     b->order = order;
     build_items(b);
-    b->items_uploaded = false;
   }
   return PMC_OK;
 }
@@ -279,10 +278,12 @@ static pmc_status batch_capture(pmc_batch* b, uint8_t* ws, uint8_t* streams) {
 }
 
 // upload the job table (current input pointers) for components [c0, c1) of
-// every field, and the items if they are not there; waits for the copies
+// every field and, with the first of them, the items, in one copy; waits for
+// it.  Every call uploads both: the workspace is the caller's, who may pass
+// another one or have used this one for something else since the last call.
 static pmc_status batch_upload(pmc_batch* b, const void* const* d_x, uint8_t* ws, uint8_t* streams, int c0, int c1) {
   pmc_ctx* ctx = b->ctx;
-  std::vector<FieldJob> tab(b->nf);
+  FieldJob* tab = (FieldJob*)b->upload.data();
   for (int i = 0; i < b->nf; ++i) {
     FieldJob& d = tab[i];
     std::memset(&d, 0, sizeof(d));
@@ -301,16 +302,11 @@ static pmc_status batch_upload(pmc_batch* b, const void* const* d_x, uint8_t* ws
       d.minexp[c] = b->minexp[i][c];
     }
   }
-  hipError_t e = hipMemcpyAsync(ws + b->off_table, tab.data(), tab.size() * sizeof(FieldJob),
-                                hipMemcpyHostToDevice, ctx->stream);
-  if (e == hipSuccess && !b->items_uploaded) {
-    e = hipMemcpyAsync(ws + b->off_items, b->items.data(), b->items.size() * sizeof(Item), hipMemcpyHostToDevice,
-                       ctx->stream);
-  }
+  const size_t bytes = c0 == 0 ? b->upload.size() : b->nf * sizeof(FieldJob);
+  hipError_t e = hipMemcpyAsync(ws + b->off_table, b->upload.data(), bytes, hipMemcpyHostToDevice, ctx->stream);
   if (e != hipSuccess) return hipfail(ctx, e, "table upload");
-  // the host vectors above are pageable: wait for the copies before they go
+  // the host buffer is pageable and is written again by the next upload
   if ((e = hipStreamSynchronize(ctx->stream)) != hipSuccess) return hipfail(ctx, e, "sync");
-  b->items_uploaded = true;
   return PMC_OK;
 }
 

@@ -108,6 +108,29 @@ def test_batch_inputs_can_change(setup):
     torch.cuda.synchronize()
 
 
+def test_workspace_may_change_between_calls(setup):
+    """Nothing of a call's tables is expected in the workspace: another one,
+    and the same one written over in between, give the oracle's streams."""
+    import torch
+    ctx, xs, taus, oracle, dev, batch = setup
+    first = batch.ws
+    for ws in (first, torch.full_like(first, 0xFF), first, torch.full_like(first, 0xFF)):
+        batch.ws = ws
+        for fill in (None, 0xFF):
+            if fill is not None:
+                ws.fill_(fill)
+            got = streams_of(batch.compress(dev))
+            for f in range(len(xs)):
+                for i in range(len(oracle[f][0])):
+                    assert np.array_equal(got[f][i], oracle[f][0][i]), (f, i)
+    batch.ws = torch.full_like(first, 0xFF)
+    batch.tune(dev)
+    got = streams_of(batch.compress(dev))
+    batch.ws = first
+    assert all(np.array_equal(got[f][i], oracle[f][0][i]) for f in range(len(xs)) for i in range(len(oracle[f][0])))
+    torch.cuda.synchronize()
+
+
 def test_full_batched_config():
     """The batched workload at its full size, in the tuned schedule the bench
     times: 256 fields, edges log-uniform in [16, 256] per axis, float32 and
