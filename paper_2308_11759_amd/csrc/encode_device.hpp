@@ -207,7 +207,7 @@ __device__ __forceinline__ void plane_emit(BitOr<kGuard>& w, uint64_t wd, uint32
     uint64_t slo = tlo | (tlo << 1) | 1ull, shi = thi | (thi << 1) | (tlo >> 63);
     const uint32_t a = lastt + 1u;
     if (a < 64u) slo &= ~(1ull << a);
-    else shi &= ~(1ull << (a - 64u));
+    else if (a < 128u) shi &= ~(1ull << (a - 64u));  // (128: all 64 coefficients new, the last one implied)
     if (implied) {
       if (lastt < 64u) slo &= ~(1ull << lastt);
       else shi &= ~(1ull << (lastt - 64u));
