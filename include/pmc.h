@@ -156,7 +156,10 @@ pmc_status pmc_compress_sizes(const pmc_field* f, int n, size_t* ws_bytes, size_
  * (capacity streams_cap bytes), which must stay alive as long as the store.
  * On success *out holds per-component metadata: prescribed tau and measured
  * max|x - x~_i| in float64 (Sec. 4.3, last paragraph), stream bytes, block
- * counts.  Synchronises the stream once at the end to read the sizes.
+ * counts.  Synchronises the stream once at the end to read the sizes; where
+ * some 64 blocks' components together need more than the workspace stages for
+ * them (about 96 bits per float32 and 192 per float64 value), the components
+ * that did not fit follow in further launches, each with its synchronisation.
  * PMC_E_BOUND still returns the store (valid streams; some blocks exceed
  * their tolerance, counted as misses); the caller frees it. */
 pmc_status pmc_compress(pmc_ctx* ctx, const pmc_field* f, const void* d_x, int n, const double* tau,
@@ -273,7 +276,10 @@ pmc_status pmc_batch_sizes(const pmc_batch* b, size_t* ws_bytes, size_t* streams
 pmc_status pmc_batch_schedule(pmc_batch* b, int grid_mult, int order);
 pmc_status pmc_batch_get_schedule(const pmc_batch* b, int* grid_mult, int* order);
 /* d_x[i]: field i on the device.  out[i] receives a store per field whose
- * streams live in d_streams.  Synchronises once to read the sizes. */
+ * streams live in d_streams.  Synchronises after the upload of the batch's
+ * tables and once more to read the sizes (d_ws keeps nothing between calls);
+ * fields that need more staging than d_ws has for them (as in pmc_compress)
+ * go on in further launches outside the graph, the others are left alone. */
 pmc_status pmc_batch_compress(pmc_batch* b, const void* const* d_x, void* d_ws, size_t ws_bytes, void* d_streams,
                               size_t streams_cap, pmc_store** out);
 /* Autotuner: times every schedule (grid_mult 1, 2, 4, 8 x 3 orders) on these

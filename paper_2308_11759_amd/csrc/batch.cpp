@@ -277,32 +277,37 @@ static pmc_status batch_capture(pmc_batch* b, uint8_t* ws, uint8_t* streams) {
   return PMC_OK;
 }
 
-// upload the job table (current input pointers) for components [c0, c1) of
-// every field and, with the first of them, the items, in one copy; waits for
-// it.  Every call uploads both: the workspace is the caller's, who may pass
-// another one or have used this one for something else since the last call.
-static pmc_status batch_upload(pmc_batch* b, const void* const* d_x, uint8_t* ws, uint8_t* streams, int c0, int c1) {
+// field i's job: its layout and where its streams go
+static bool batch_job(const pmc_batch* b, int i, uint8_t* ws, uint8_t* streams, bool resumed, FieldJob* d) {
+  if (!job_layout(&b->f[i], b->g[i], b->n[i], resumed, ws + b->off_job[i], b->job_bytes[i], d)) return false;
+  d->region = streams + b->region_off[i];
+  d->aux_stride = aux_bytes(b->g[i]) / 4;
+  d->meta = (CompMeta*)(ws + b->off_meta) + b->meta_first[i];
+  d->region_cap = b->region_cap[i];
+  return true;
+}
+
+// upload the job table (current input pointers) and the items in one copy;
+// waits for it.  Every call uploads both: the workspace is the caller's, who
+// may pass another one or have used this one for something else since the last
+// call.  from (NULL: 0 for every field): the table alone, for a further round
+// of launches that take field i's components from from[i] on (its n: none).
+static pmc_status batch_upload(pmc_batch* b, const void* const* d_x, uint8_t* ws, uint8_t* streams, const int* from) {
   pmc_ctx* ctx = b->ctx;
   FieldJob* tab = (FieldJob*)b->upload.data();
   for (int i = 0; i < b->nf; ++i) {
     FieldJob& d = tab[i];
     std::memset(&d, 0, sizeof(d));
-    if (!job_layout(&b->f[i], b->g[i], b->n[i], b->n[i] > 1 && (c0 > 0 || c1 < b->maxn), ws + b->off_job[i],
-                    b->job_bytes[i], &d))
+    if (!batch_job(b, i, ws, streams, from && from[i] < b->n[i], &d))
       return fail(ctx, PMC_E_NOMEM, "field %d: workspace too small for its layout", i);
     d.x = d_x[i];
-    d.comp0 = (uint8_t)std::min(c0, b->n[i]);
-    d.comp1 = (uint8_t)std::min(c1, b->n[i]);
-    d.region = streams + b->region_off[i];
-    d.aux_stride = aux_bytes(b->g[i]) / 4;
-    d.meta = (CompMeta*)(ws + b->off_meta) + b->meta_first[i];
-    d.region_cap = b->region_cap[i];
+    d.comp0 = (uint8_t)(from ? from[i] : 0);
     for (int c = 0; c < b->n[i]; ++c) {
       d.tau[c] = b->tau[i][c];
       d.minexp[c] = b->minexp[i][c];
     }
   }
-  const size_t bytes = c0 == 0 ? b->upload.size() : b->nf * sizeof(FieldJob);
+  const size_t bytes = from ? b->nf * sizeof(FieldJob) : b->upload.size();
   hipError_t e = hipMemcpyAsync(ws + b->off_table, b->upload.data(), bytes, hipMemcpyHostToDevice, ctx->stream);
   if (e != hipSuccess) return hipfail(ctx, e, "table upload");
   // the host buffer is pageable and is written again by the next upload
@@ -313,7 +318,7 @@ static pmc_status batch_upload(pmc_batch* b, const void* const* d_x, uint8_t* ws
 // upload, then replay the graph (captured again when buffers or schedule changed)
 static pmc_status batch_launch(pmc_batch* b, const void* const* d_x, uint8_t* ws, uint8_t* streams) {
   pmc_ctx* ctx = b->ctx;
-  pmc_status st = batch_upload(b, d_x, ws, streams, 0, b->maxn);
+  pmc_status st = batch_upload(b, d_x, ws, streams, nullptr);
   if (st != PMC_OK) return st;
   if (!b->exec || b->g_ws != ws || b->g_streams != streams || b->g_grid != b->grid_mult || b->g_order != b->order) {
     st = batch_capture(b, ws, streams);
@@ -365,13 +370,32 @@ pmc_status pmc_batch_compress(pmc_batch* b, const void* const* d_x, void* d_ws, 
     return r;
   };
   if ((e = results()) != hipSuccess) return hipfail(ctx, e, "meta copy");
-  if ((flags & FLAG_STAGING) && !(flags & FLAG_NONFINITE)) {
-    // the components of some wave did not fit its slot together: one round
-    // of launches per component
-    for (int c = 0; c < b->maxn; ++c) {
-      if ((st = batch_upload(b, d_x, ws, streams, c, c + 1)) != PMC_OK) return st;
-      if ((e = batch_kernels(b, ws, 1, ctx->stream)) != hipSuccess) return hipfail(ctx, e, "encode");
+  // fields of which some wave's components did not fit its slot together go on
+  // from the first that did not (as in pmc_compress); the others are done (24
+  // fields and a small incompressible one: 1.25 ms, of which the 24 take 0.63;
+  // every field again, a round of launches per component, took 3.1).
+  std::vector<int> done(b->nf, 0), next(b->nf);
+  while ((flags & FLAG_STAGING) && !(flags & (FLAG_NONFINITE | FLAG_INDEX | FLAG_OVERFLOW))) {
+    int comps = 0;
+    for (int i = 0; i < b->nf; ++i) {
+      const CompMeta* m = hm.data() + b->meta_first[i];
+      next[i] = first_over(m, done[i], b->n[i]);
+      if (next[i] == b->n[i]) continue;
+      if (next[i] == done[i]) return fail(ctx, PMC_E_DEVICE, "field %d: a component outgrew its staging slot", i);
+      FieldJob d{};
+      if (!batch_job(b, i, ws, streams, true, &d))
+        return fail(ctx, PMC_E_NOMEM, "field %d: workspace too small for its layout", i);
+      e = resume_job(ctx, &b->f[i], b->g[i], b->n[i], b->tau[i].data(), b->minexp[i].data(), m, 0, done[i], next[i], &d);
+      if (e != hipSuccess) return hipfail(ctx, e, "decode");
+      comps = std::max(comps, b->n[i] - next[i]);
     }
+    done = next;
+    if ((st = batch_upload(b, d_x, ws, streams, done.data())) != PMC_OK) return st;
+    {
+      ProfScope ps(ctx, "batch_resumed");
+      e = batch_kernels(b, ws, comps, ctx->stream);
+    }
+    if (e != hipSuccess) return hipfail(ctx, e, "encode");
     if ((e = results()) != hipSuccess) return hipfail(ctx, e, "meta copy");
   }
   if (flags & FLAG_NONFINITE) return fail(ctx, PMC_E_NONFINITE, "input holds NaN or Inf");

@@ -241,6 +241,50 @@ __device__ __forceinline__ void load_rows(const T* f, const Geo& g, const BlockP
   }
 }
 
+// Where x~ goes from one launch of the encoder to the next it is kept in one
+// tile per wave, the wave's 64 blocks as [row r][lane][16-byte piece]
+// (float32: 4 values; float64: [row r][half][lane][2 values]): coalesced
+// whatever the field's shape, and the layout the encoder has x in in LDS.
+constexpr uint64_t kTileValues = 64 * 64;  // values of one wave's tile
+template <class T> __device__ __forceinline__ uint32_t tile_index(uint32_t lane, int r, int t) {
+  if constexpr (sizeof(T) == 4) return ((uint32_t)r * 64 + lane) * 4 + (uint32_t)t;
+  else return (((uint32_t)r * 2 + (uint32_t)(t >> 1)) * 64 + lane) * 2 + (uint32_t)(t & 1);
+}
+// (job pointers come out of constant memory as generic ones: the accesses name
+// the global address space, or they would be flat instructions)
+template <class T> using gptr = __attribute__((address_space(1))) T*;
+template <class T> __device__ __forceinline__ gptr<T> to_global(T* p) { return (gptr<T>)p; }
+// row r of this lane's block from a wave's tile
+template <class T> __device__ __forceinline__ void tile_load_row(gptr<const T> tile, uint32_t lane, int r, T v[4]) {
+  if constexpr (sizeof(T) == 4) {
+    const nt_f4 q = *(gptr<const nt_f4>)(tile + tile_index<T>(lane, r, 0));
+    v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
+  } else {
+    const nt_d2 q0 = *(gptr<const nt_d2>)(tile + tile_index<T>(lane, r, 0));
+    const nt_d2 q1 = *(gptr<const nt_d2>)(tile + tile_index<T>(lane, r, 2));
+    v[0] = q0.x; v[1] = q0.y; v[2] = q1.x; v[3] = q1.y;
+  }
+}
+// row r of this lane's block into a wave's tile
+template <class T> __device__ __forceinline__ void tile_store_row(gptr<T> tile, uint32_t lane, int r, const T v[4]) {
+  if constexpr (sizeof(T) == 4) {
+    *(gptr<nt_f4>)(tile + tile_index<T>(lane, r, 0)) = nt_f4{v[0], v[1], v[2], v[3]};
+  } else {
+    *(gptr<nt_d2>)(tile + tile_index<T>(lane, r, 0)) = nt_d2{v[0], v[1]};
+    *(gptr<nt_d2>)(tile + tile_index<T>(lane, r, 2)) = nt_d2{v[2], v[3]};
+  }
+}
+// the whole block of lane `lane` of wave w
+template <class T> __device__ __forceinline__ void tile_load(const T* tiles, uint64_t w, uint32_t lane, T v[64]) {
+  const gptr<const T> tile = to_global(tiles) + w * kTileValues;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) tile_load_row<T>(tile, lane, r, v + 4 * r);
+}
+template <class T> __device__ __forceinline__ void tile_store(T* tiles, uint64_t w, uint32_t lane, const T v[64]) {
+  const gptr<T> tile = to_global(tiles) + w * kTileValues;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) tile_store_row<T>(tile, lane, r, v + 4 * r);
+}
 
 __device__ __forceinline__ BlockPos opaque_pos(BlockPos b) {
   b.x0 = opaque(b.x0);

@@ -8,6 +8,7 @@
 //  k_decode_split    either, with one wave per component (fields and boxes of
 //                    few waves)
 //  k_decode_queries  many retrievals in one launch
+//  k_decode_tiles    x~ for the encoder to go on from
 #pragma once
 #include "block_device.hpp"
 
@@ -208,7 +209,7 @@ __device__ __forceinline__ bool decode_block_codec(R& r, int minexp, double step
   else return pq_decode_add<T>(r, step, acc);
 }
 
-template <class T, bool kStaged, bool kBox = false, bool kFull = false, int kCodec = 0, bool kHiRes = false>
+template <class T, bool kStaged, bool kBox = false, bool kFull = false, int kCodec = 0, bool kHiRes = false, bool kTile = false>
 __device__ __forceinline__ bool decode_wave(const Geo& g, const uint8_t* const* s, const uint32_t* const* aux,
                                             const uint64_t* words, const int* minexp, const double* step, int ncomp,
                                             uint32_t relmask, const T* in, T* out, uint64_t w, const uint8_t* sq,
@@ -238,6 +239,7 @@ __device__ __forceinline__ bool decode_wave(const Geo& g, const uint8_t* const* 
   }
   if (in && active) {
     if constexpr (kBox) load_box(in, *box, bp, acc);
+    else if constexpr (kTile) tile_load<T>(in, w, lane, acc);
     else if constexpr (kFull) load_rows<T, 16>(in, g, opaque_pos(bp), 0, true, acc);
     else load_block(in, g, opaque_pos(bp), acc);
   } else {
@@ -367,6 +369,8 @@ __device__ __forceinline__ bool decode_wave(const Geo& g, const uint8_t* const* 
   if (active) {
     if constexpr (kBox) {
       store_box(out, *box, block_pos(g, opaque(w) * 64 + lane), acc);
+    } else if constexpr (kTile) {
+      tile_store<T>(out, w, lane, acc);
     } else if constexpr (kFull) {
       const BlockPos bo = block_pos(g, opaque(w) * 64 + lane);
 #pragma unroll
@@ -391,6 +395,18 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
   squeeze_table(s_squeeze);
   if (!decode_wave<T, kStaged, false, kFull, kCodec, kHiRes>(a.g, a.s, a.aux, a.words, a.minexp, a.step, a.ncomp, a.relmask,
                                                      a.in, a.out, blockIdx.x, s_squeeze, s_stage))
+    atomicOr(a.status, 1u);
+}
+
+// x~ as the encoder takes it up (a.in and a.out hold one tile per wave), from
+// components in place; once per launch of the encoder after the first, so the
+// plain reader and routes do
+template <class T, int kCodec>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 3 : 1))) void k_decode_tiles(DecArgs<T> a) {
+  __shared__ uint8_t s_squeeze[256];
+  squeeze_table(s_squeeze);
+  if (!decode_wave<T, false, false, false, kCodec, false, true>(a.g, a.s, a.aux, a.words, a.minexp, a.step, a.ncomp,
+                                                                a.relmask, a.in, a.out, blockIdx.x, s_squeeze, nullptr))
     atomicOr(a.status, 1u);
 }
 
@@ -658,6 +674,12 @@ hipError_t launch_decode_box(const DecArgs<T>& a, const BoxArgs& b, uint64_t max
     if (staged) hipLaunchKernelGGL((k_decode_box<T, true, 1>), grid, wg, 0, s, a, b);
     else hipLaunchKernelGGL((k_decode_box<T, false, 1>), grid, wg, 0, s, a, b);
   }
+  return hipGetLastError();
+}
+template <class T> hipError_t launch_decode_tiles(const DecArgs<T>& a, int codec, hipStream_t s) {
+  const dim3 grid((uint32_t)((a.g.nblocks + 63) / 64)), wg(64);
+  if (codec == 0) hipLaunchKernelGGL((k_decode_tiles<T, 0>), grid, wg, 0, s, a);
+  else hipLaunchKernelGGL((k_decode_tiles<T, 1>), grid, wg, 0, s, a);
   return hipGetLastError();
 }
 template <class T>

@@ -43,39 +43,6 @@ template <class T> struct XLds {
   __device__ __forceinline__ T at(int l) const { return *slot(l >> 2, l & 3); }
 };
 
-// Where x~ has to outlive a launch (components run one launch each) it is kept
-// in one tile per wave, the wave's 64 blocks as [row r][lane][16-byte piece]
-// (float32: 4 values; float64: [row r][half][lane][2 values]), the layout XLds
-// uses in LDS.
-constexpr uint64_t kTileValues = 64 * 64;  // values of one wave's tile
-template <class T> __device__ __forceinline__ uint32_t tile_index(uint32_t lane, int r, int t) {
-  if constexpr (sizeof(T) == 4) return ((uint32_t)r * 64 + lane) * 4 + (uint32_t)t;
-  else return (((uint32_t)r * 2 + (uint32_t)(t >> 1)) * 64 + lane) * 2 + (uint32_t)(t & 1);
-}
-// (job pointers come out of constant memory as generic ones: the accesses name
-// the global address space, or they would be flat instructions)
-template <class T> using gptr = __attribute__((address_space(1))) T*;
-template <class T> __device__ __forceinline__ gptr<T> to_global(T* p) { return (gptr<T>)p; }
-// row r of this lane's block from a wave's tile
-template <class T> __device__ __forceinline__ void tile_load_row(gptr<const T> tile, uint32_t lane, int r, T v[4]) {
-  if constexpr (sizeof(T) == 4) {
-    const nt_f4 q = *(gptr<const nt_f4>)(tile + tile_index<T>(lane, r, 0));
-    v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
-  } else {
-    const nt_d2 q0 = *(gptr<const nt_d2>)(tile + tile_index<T>(lane, r, 0));
-    const nt_d2 q1 = *(gptr<const nt_d2>)(tile + tile_index<T>(lane, r, 2));
-    v[0] = q0.x; v[1] = q0.y; v[2] = q1.x; v[3] = q1.y;
-  }
-}
-// row r of this lane's block into a wave's tile
-template <class T> __device__ __forceinline__ void tile_store_row(gptr<T> tile, uint32_t lane, int r, const T v[4]) {
-  if constexpr (sizeof(T) == 4) {
-    *(gptr<nt_f4>)(tile + tile_index<T>(lane, r, 0)) = nt_f4{v[0], v[1], v[2], v[3]};
-  } else {
-    *(gptr<nt_d2>)(tile + tile_index<T>(lane, r, 0)) = nt_d2{v[0], v[1]};
-    *(gptr<nt_d2>)(tile + tile_index<T>(lane, r, 2)) = nt_d2{v[2], v[3]};
-  }
-}
 // edge replication of a partial block's residual, in registers: each padded
 // sample takes the value of the last valid sample on each axis (x, then y,
 // then z), as the block gather of a partial block does
@@ -631,7 +598,7 @@ __device__ __forceinline__ void encode_wave(const F& f, uint32_t wave, T* s_x, u
       cw3 = ((uint32_t)__builtin_amdgcn_readlane((int)incl, 63) + 31u) / 32u;
       tot = cw0 + cw1 + cw2 + cw3;
       // the span goes behind the earlier ones in the slot; where it does not
-      // fit, the host runs the components one by one
+      // fit, a later launch goes on from here
       const uint32_t need = (tot + 3u) & ~3u;
       start = cur;
       over = cur + need > limit;

@@ -62,9 +62,14 @@ uint64_t stream_cap_one(const pmc::Geo& g, int dtype);
 // components' results (CompMeta), and its layout: fills the job's pointers
 // into ws (bytes of them) and its sizes; false if it does not fit
 uint64_t job_workspace(const pmc_field* f, const pmc::Geo& g, int n);
-// apart: for components in one launch each
-bool job_layout(const pmc_field* f, const pmc::Geo& g, int n, bool apart, uint8_t* ws, uint64_t bytes,
+// resumed: for a launch that goes on from x~ of the components before it
+bool job_layout(const pmc_field* f, const pmc::Geo& g, int n, bool resumed, uint8_t* ws, uint64_t bytes,
                 pmc::FieldJob* job);
+// the first component at or after `from` that outgrew a wave's staging slot (n: none)
+int first_over(const pmc::CompMeta* hm, int from, int n);
+// the job's x~ tiles taken on from component done to next, which are in place in the region
+hipError_t resume_job(pmc_ctx* ctx, const pmc_field* f, const pmc::Geo& g, int n, const double* tau, const int* minexp,
+                      const pmc::CompMeta* hm, int codec, int done, int next, pmc::FieldJob* job);
 // a store from per-component device results (offsets relative to d_base)
 pmc_store* store_from_meta(const pmc_field* f, const pmc::Geo& g, int n, const double* tau, const int* minexp,
                            const pmc::CompMeta* hm, const uint8_t* d_base, int codec);

@@ -66,7 +66,7 @@ constexpr uint32_t kStatNotHi32 = 1u << 31;    // kNotHi32 of a block
 struct FieldJob {
   const void* x;
   Geo g;
-  void* tiles;        // x~ of every wave between launches (64 * 64 values each), where components run one launch each
+  void* tiles;        // x~ of every wave between launches (64 * 64 values each), where components take several
   uint32_t* staging;  // wave w's slot at w * slot_words
   uint32_t slot_words, slot_last;  // words of a slot, of the last wave's
   uint32_t* chunk_words;  // [component][chunk]
@@ -196,6 +196,8 @@ hipError_t launch_decode(const DecArgs<T>& a, uint64_t max_span, int codec, bool
 template <class T>
 hipError_t launch_decode_box(const DecArgs<T>& a, const BoxArgs& b, uint64_t max_span, int codec, bool hires,
                              const SplitArgs* split, hipStream_t s);
+// components [0, a.ncomp) added to the encoder's x~ tiles (FieldJob::tiles) at a.in, into those at a.out
+template <class T> hipError_t launch_decode_tiles(const DecArgs<T>& a, int codec, hipStream_t s);
 uint64_t stage_words();  // capacity of the decoder's LDS staging buffer, in words
 // min / max / non-finite count of n samples: one partial of kRangeWords words
 // per workgroup at out; range_groups: how many workgroups suit n, at most

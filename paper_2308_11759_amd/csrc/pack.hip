@@ -18,8 +18,6 @@
 namespace pmc {
 
 typedef __attribute__((address_space(4))) const FieldJob CFieldJob;
-template <class T> using gptr = __attribute__((address_space(1))) T*;
-template <class T> __device__ __forceinline__ gptr<T> to_global(T* p) { return (gptr<T>)p; }
 typedef uint32_t u4_any __attribute__((ext_vector_type(4), aligned(4)));  // a 16-byte access at any word
 
 // (k_pack: 16 waves, so that the few tiles of a small field move four spans per
