@@ -666,7 +666,7 @@ static pmc_status decode_range(pmc_ctx* ctx, const pmc_store* s, int k0, int k1,
   const void* in = d_in;
   for (int i0 = k0, i1; i0 < k1; i0 = i1) {
     SplitArgs sp;
-    const SplitArgs* psp = ctx->fused_decode && split_plan(s, i0, k1, waves, &i1, &sp) ? &sp : nullptr;
+    const SplitArgs* psp = ctx->fused_decode && split_plan(s, i0, k1, waves, false, &i1, &sp) ? &sp : nullptr;
     if (!psp) i1 = std::min(i0 + (ctx->fused_decode ? kMaxDecode : 1), k1);
     uint64_t span = 0;
     for (int i = i0; i < i1; ++i) span = std::max(span, s->max_span[i]);
@@ -729,16 +729,11 @@ pmc_status pmc_retrieve_box(pmc_ctx* ctx, const pmc_store* s, int k, const uint6
   const uint64_t nbx = b.bhi[0] - b.blo[0];
   const bool whole = s->g.nbx % 64 == 0;
   b.waves_per_row = (uint32_t)(whole ? (b.blo[0] % 64 + nbx + 63) / 64 : (nbx + 63) / 64 + 1);
-  // for the split's cost rule: the waves launched, those that find no block
-  // (all but about (63 + nbx) / 64 of a row) at half (300^3, 8 components, a
-  // 100^3 box: 625 rows, one wave per component 76 us, one for all 70; 64^3:
-  // 256 rows, 35 / 64; 256^3, 100^3: 48 / 53)
-  const uint64_t rows = (b.bhi[1] - b.blo[1]) * (b.bhi[2] - b.blo[2]);
-  const uint64_t waves = whole ? rows * b.waves_per_row : rows * (63 + nbx + 64ull * b.waves_per_row) / 128;
+  const uint64_t waves = (b.bhi[1] - b.blo[1]) * (b.bhi[2] - b.blo[2]) * b.waves_per_row;
   const void* in = nullptr;
   for (int i0 = 0, i1; i0 < k; i0 = i1) {
     SplitArgs sp;
-    const SplitArgs* psp = split_plan(s, i0, k, waves, &i1, &sp) ? &sp : nullptr;
+    const SplitArgs* psp = split_plan(s, i0, k, waves, true, &i1, &sp) ? &sp : nullptr;
     if (!psp) i1 = std::min(i0 + kMaxDecode, k);
     uint64_t span = 0;
     for (int i = i0; i < i1; ++i) span = std::max(span, s->max_span[i]);

@@ -443,10 +443,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
 // through LDS, a few of a block's 16 rows at a time, in the memory the words
 // were staged in.  64^3 float32, 8 components (64 waves): 44.9 us, now 17.4; a
 // 64^3 box of a 512^3 field 66, now 31.
+// (float32 asks for three waves per SIMD, 168 registers, as split_plan counts:
+// the box on the high-half routes had come out at 169 and two)
 template <class T, bool kHiRes> constexpr int split_most() { return sizeof(T) == 4 || kHiRes ? kMaxSplit : kMaxSplit64; }
 template <class T, bool kBox, int kCodec, bool kHiRes>
 __global__ __launch_bounds__((64 * split_most<T, kHiRes>()))
-    __attribute__((amdgpu_waves_per_eu((split_most<T, kHiRes>() / 4)))) void k_decode_split(
+    __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 3 : split_most<T, kHiRes>() / 4))) void k_decode_split(
     DecArgs<T> a, SplitArgs sp, BoxArgs b) {
   extern __shared__ __attribute__((aligned(16))) uint32_t s_dyn[];  // sp.lds_bytes
   __shared__ uint8_t s_squeeze[256];
@@ -569,7 +571,7 @@ __global__ __launch_bounds__((64 * split_most<T, kHiRes>()))
       // (a block whose stream did not parse: quiet NaNs, as in decode_wave)
       if (!((good >> lane) & 1u)) v[0] = v[1] = v[2] = v[3] = (T)__builtin_nan("");
       if (active) {
-        const BlockPos bp = block_pos(g, blk);
+        const BlockPos bp = block_pos(g, opaque(w) * 64 + lane);
         if constexpr (kBox) store_box_row(a.out, b, bp, (int)(s + rr), v);
         else store_row(a.out, g, bp, (int)(s + rr), v);
       }

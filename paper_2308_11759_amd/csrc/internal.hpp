@@ -99,21 +99,39 @@ inline bool high_half(const pmc_store* s, int i0, int i1) {
 
 // The next launch [i0, i1) of a retrieval of components [i0, k), and its
 // staging plan if it decodes `waves` waves of blocks with one wave per
-// component (k_decode_split); false where one wave decodes all of them.
+// component (k_decode_split); false where one wave decodes all of them.  For a
+// box, `waves` counts the workgroups launched, those that meet no block of it
+// too.
 //
 // A launch takes up to eight components (float64 off the high-half routes
 // four: 850 spills at the 256 registers of eight), launches of about the same
 // size and as few as there can be, and asks for at most 64 KB of LDS per
-// workgroup.  It is taken where few rounds of workgroups cover the field: one
-// wave costs about 5 us per component while the chip is not full, a round of
-// workgroups 13 (float64 16).  Measured (us, one wave / split): float32, 8
-// components: 64 waves 44.9 / 17.4, 512 (2 rounds) 47.1 / 30.6, 729 (3) 46.6 /
-// 42.2, 1000 (4) 46.6 / 53.5; 6: 512 (2) 43.8 / 31.6, 729 (3) 43.5 / 43.7; 4:
-// 1000 (2) 32.2 / 31.1; 3: 1000 (1) 27.3 / 25.5; 2: 216 (1) 20.1 / 18.2, 1954
-// (2) 29.5 / 39.6.  float64, 8: 64 waves 44.1 / 22.2, 512 (2) 46.9 / 40.5, 729
-// (3) 49.6 / 57.4; off the high-half routes, 4: 216 (1) 31.5 / 18.8; 6 in two
-// launches: 64 41.3 / 36.6, 343 (2) 42.4 / 66.5.
-inline bool split_plan(const pmc_store* s, int i0, int k, uint64_t waves, int* i1, pmc::SplitArgs* sp) {
+// workgroup.  It is taken where few rounds of workgroups cover the field: the
+// time goes in steps, one per round, and one wave for all components takes
+// nearly the same time until the chip is full.  A CU holds as many workgroups
+// as fit its registers' 12 waves (float32; float64 8 on the high-half routes,
+// else 4), but one of five or more components alone.  Measured (us, one wave
+// for all / one per component, cubes; the worse side of each line and the
+// better one next to it):
+//   float32  8 components, 512 waves (2 rounds) 48 / 31, 729 (3) 48 / 43, 858 (4)
+//            48 / 55; 7: 729 (3) 42 / 42; 6: 512 (2) 37 / 30, 729 (3) 37 / 41
+//            (off the high-half routes 50 / 45, codec 1 34 / 32, boxes 50 / 46);
+//            5: 512 (2) 32 / 29, 615 (3) 33 / 41
+//            4: 729 (1) 28 / 22, 858 (2) 29 / 31 (boxes 41 / 35; off the
+//            high-half routes 35 / 32, codec 1 26 / 23), 1728 (3) 46 / 49
+//            3: 1000 (1) 25 / 24, 1331 (2) 30 / 39
+//            2: 216 (1) 19.2 / 18.6, 275 (1) 20.0 / 20.7 (off the high-half
+//            routes 729 21.2 / 19.4, 858 21.5 / 22.5; boxes 1352 29 / 28)
+//   float64  8: 512 (2) 48 / 41, 615 (3) 48 / 58; 6: 422 (2) 38 / 38; 5: 275
+//            (2) 33 / 37; 4: 512 (1) 30 / 23, 615 (2) 31 / 36; 2: 1000 (1) 26 / 23,
+//            1331 (2) 29 / 38; off the high-half routes 4: 245 (1) 37 / 22, 275
+//            (2) 38 / 37; 3: 275 (2) 29 / 35; 6 in two launches: 245 (1) 52 / 40,
+//            275 (2) 53 / 70
+//   more components than a launch takes (one wave for all takes sixteen):
+//            float32 9: 343 (2) 44 / 41, 10: 48 / 50 (codec 1 48 / 44), 12: 512 (2)
+//            56 / 53, 729 (3) 56 / 76, 16: 729 (3) 75 / 82 (codec 1 75 / 69);
+//            float64 12: 343 (2) 64 / 72, 16: 81 / 78
+inline bool split_plan(const pmc_store* s, int i0, int k, uint64_t waves, bool box, int* i1, pmc::SplitArgs* sp) {
   const bool f32 = s->f.dtype == PMC_F32;
   int most = pmc::kMaxSplit, n = 0, launches = 0;
   bool hires = false;
@@ -136,9 +154,21 @@ inline bool split_plan(const pmc_store* s, int i0, int k, uint64_t waves, int* i
   const uint64_t lds = std::max(words * 4, (uint64_t)n * 4096);  // the words, then 4 KB of rows per component
   if (lds > 65536 - 512) return false;
   const uint64_t slots = f32 ? 12 : hires ? 8 : 4;  // waves a CU's registers hold
-  const uint64_t resident = 256 * std::min(slots / n, 163840 / (lds + 512));
-  const uint64_t rounds = (waves + resident - 1) / resident;
-  if ((f32 ? 13 : 16) * rounds * launches > 5 * (uint64_t)(k - i0) + 6) return false;
+  const uint64_t resident = std::min<uint64_t>(n > 4 ? 1 : slots / n, 163840 / (lds + 512));
+  const uint64_t rounds = (waves + 256 * resident - 1) / (256 * resident);
+  uint64_t most_rounds = 1;
+  if (launches > 1) {
+    if (f32) most_rounds = n == 8 && !hires ? 3 : n >= 6 || !hires || k - i0 == 9 ? 2 : 1;
+    else if (hires) most_rounds = n == 8 ? 2 : 1;
+    else if (k - i0 < 6) return false;
+  } else if (f32) {
+    if (n >= 5) most_rounds = n >= 7 || (n == 6 && (box || !hires)) ? 3 : 2;
+    if (n == 4 && (box || !hires)) most_rounds = 2;
+    if (n == 2 && !box && waves > (hires || s->codec != 0 ? 256u : 768u)) return false;
+  } else if (n >= 6) {
+    most_rounds = 2;
+  }
+  if (rounds > most_rounds) return false;
   sp->lds_bytes = (uint32_t)lds;
   *i1 = i0 + n;
   return true;
