@@ -568,8 +568,12 @@ __device__ __forceinline__ void dequant_add(const int64_t q[64], int emax, doubl
 // the coefficients are multiples of 2^54, the words the lifting forms are
 // multiples of 2^48, and their top 16 bits h follow the same packed lifting;
 // q = h * 2^48 is exact in double, so q * 2^(emax-62) = h * 2^(emax-14),
-// computed exactly while it is normal (emax >= -1008), is what dequantize()
-// gives, and the fused multiply-add of that exact product is acc + it.
+// computed exactly while it is normal (emax >= -1008) and finite (|h| <= 2^15:
+// emax <= 1022; beyond, the fused sum of a product that overflows need not), is
+// what dequantize() gives, and the fused multiply-add of that exact product is
+// acc + it.
+__device__ __forceinline__ bool hi16_exact(int emax, float) { return fast_dequant(emax); }
+__device__ __forceinline__ bool hi16_exact(int emax, double) { return emax >= -1008 && emax <= 1022; }
 template <class T> __device__ __forceinline__ T hi16_scale(int emax);
 template <> __device__ __forceinline__ float hi16_scale<float>(int emax) {
   return __uint_as_float((uint32_t)(emax - 14 + 127) << 23);
@@ -886,8 +890,9 @@ __device__ __forceinline__ void slots_hi16(R& r, int p, int zlead, const uint8_t
 // positions, its exponent keeping the scaled values normal), kNotHi32 when a
 // float64 block is outside the high-word route (decode_hi32)
 template <class T> __device__ __forceinline__ uint32_t route_flags(int p, int emax) {
-  if constexpr (sizeof(T) == 4) return p <= 10 && fast_dequant(emax) ? 0u : kNotHi16;
-  else return (p <= 10 && emax >= -1008 ? 0u : kNotHi16) | (p <= 26 && emax >= -992 ? 0u : kNotHi32);
+  const uint32_t hi16 = p <= 10 && hi16_exact(emax, (T)0) ? 0u : kNotHi16;
+  if constexpr (sizeof(T) == 4) return hi16;
+  else return hi16 | (p <= 26 && emax >= -992 ? 0u : kNotHi32);
 }
 
 // advance a reader over one plane: plane_read without the plane's bits.  A

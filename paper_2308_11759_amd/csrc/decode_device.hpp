@@ -23,7 +23,7 @@ namespace pmc {
 // the float32 high-half route, for components whose every block has p <= 10
 // and fast_dequant(emax) (the caller guarantees it)
 // float64 fields whose blocks qualify decode in 256 registers, two waves per
-// SIMD: kRouteHi16 for the residual components (p <= 10 and emax >= -1008),
+// SIMD: kRouteHi16 for the residual components (p <= 10 and hi16_exact(emax)),
 // kRouteFirst for a store's first one (no raw blocks, p <= 26 and emax >= -992).
 // x~ takes 128 of the registers, so with every route in one loop only one wave
 // fits and its LDS latency stands open: 256^3, k = 8, 201 us, now 131.
@@ -83,9 +83,9 @@ __device__ __forceinline__ bool decode_block_add(R& r, int minexp, T acc[64], co
   if (!coded_head<T>(r, h, minexp, emax, p, zlead)) return false;
   if constexpr (sizeof(T) == 8 && kRoute == kRouteAuto) {
     // residual components whose coded planes all lie in the top ten bit
-    // positions and keep every result normal: the lifting on the words' top
+    // positions and keep every result normal and finite: the lifting on the words' top
     // 16 bits, two per register, from 4 or 8 slots (wave-uniform choices)
-    if (rel && __all(p <= 10 && emax >= -1008)) {
+    if (rel && __all(p <= 10 && hi16_exact(emax, (T)0))) {
       const int np = p - zlead;
       v2s R2[32];
       if (__all(np <= 4)) {

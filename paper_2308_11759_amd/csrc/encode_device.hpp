@@ -494,7 +494,7 @@ __device__ __forceinline__ void encode_wave(const F& f, uint32_t wave, T* s_x, u
           aw = __all(np <= 8) ? 8 : 0;
         }
         feasible = ok && cb <= (uint32_t)FT<T>::RAW_BITS;
-        if (__all(!feasible || (p <= 10 && (sizeof(T) == 4 ? fast_dequant(emax) : emax >= -1008)))) {
+        if (__all(!feasible || (p <= 10 && hi16_exact(emax, (T)0)))) {
           // planes in the top ten bit positions, every result normal: the
           // packed 16-bit lifting (see lift_dequant_add_hi16)
           const uint32_t m16 = 0xFFFFu & ~(0xFFFFu >> (p & 15)), m2 = m16 | (m16 << 16);
