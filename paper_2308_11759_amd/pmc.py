@@ -104,9 +104,9 @@ SIGNATURES = {
 }
 
 
-_new_bytes = ctypes.pythonapi.PyBytes_FromStringAndSize
-_new_bytes.restype = ctypes.py_object
-_new_bytes.argtypes = [_vp, ctypes.c_ssize_t]
+# (a function object of its own: the one ctypes.pythonapi hands out is shared
+# by everything in the process, its types included)
+_new_bytes = ctypes.PYFUNCTYPE(ctypes.py_object, _vp, ctypes.c_ssize_t)(("PyBytes_FromStringAndSize", ctypes.pythonapi))
 
 
 def load(path=LIB_PATH):
