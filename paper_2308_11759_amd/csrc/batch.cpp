@@ -333,16 +333,21 @@ static pmc_status batch_launch(pmc_batch* b, const void* const* d_x, uint8_t* ws
   return PMC_OK;
 }
 
+static pmc_status check_inputs(const pmc_batch* b, const void* const* d_x) {
+  for (int i = 0; i < b->nf; ++i) {
+    if (!d_x[i]) return fail(b->ctx, PMC_E_ARG, "field %d: null input", i);
+    if (!aligned16(d_x[i])) return fail(b->ctx, PMC_E_ARG, "field %d: input not 16-byte aligned", i);
+  }
+  return PMC_OK;
+}
+
 pmc_status pmc_batch_compress(pmc_batch* b, const void* const* d_x, void* d_ws, size_t ws_bytes, void* d_streams,
                               size_t streams_cap, pmc_store** out) {
   if (!b) return PMC_E_ARG;
   pmc_ctx* ctx = b->ctx;
   if (!d_x || !d_ws || !d_streams || !out) return fail(ctx, PMC_E_ARG, "null argument");
-  for (int i = 0; i < b->nf; ++i) {
-    out[i] = nullptr;
-    if (!d_x[i]) return fail(ctx, PMC_E_ARG, "field %d: null input", i);
-    if (!aligned16(d_x[i])) return fail(ctx, PMC_E_ARG, "field %d: input not 16-byte aligned", i);
-  }
+  for (int i = 0; i < b->nf; ++i) out[i] = nullptr;
+  if (pmc_status bad = check_inputs(b, d_x)) return bad;
   if (ws_bytes < b->ws_total)
     return fail(ctx, PMC_E_NOMEM, "workspace too small: need %llu bytes", (unsigned long long)b->ws_total);
   if (streams_cap < b->streams_total)
@@ -412,6 +417,7 @@ pmc_status pmc_batch_tune(pmc_batch* b, const void* const* d_x, void* d_ws, size
   if (!b) return PMC_E_ARG;
   pmc_ctx* ctx = b->ctx;
   if (!d_x || !d_ws || !d_streams) return fail(ctx, PMC_E_ARG, "null argument");
+  if (pmc_status bad = check_inputs(b, d_x)) return bad;
   if (ws_bytes < b->ws_total || streams_cap < b->streams_total) return fail(ctx, PMC_E_NOMEM, "buffers too small");
   hipError_t e = hipSetDevice(ctx->device);
   if (e != hipSuccess) return hipfail(ctx, e, "hipSetDevice");
