@@ -36,9 +36,6 @@ __device__ __forceinline__ BlockPos block_pos(const Geo& g, uint64_t blk) {
   return b;
 }
 
-__device__ __forceinline__ bool lvalid(const BlockPos& b, int l) {
-  return (uint32_t)(l & 3) < b.vx && (uint32_t)((l >> 2) & 3) < b.vy && (uint32_t)(l >> 4) < b.vz;
-}
 // bit l set when sample l of the block lies inside the field
 __device__ __forceinline__ uint64_t valid_mask(const BlockPos& b) {
   const uint64_t xm = (1ull << b.vx) - 1ull;                                               // a row

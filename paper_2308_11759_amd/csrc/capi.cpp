@@ -1,7 +1,7 @@
 // capi.cpp -- C-ABI of the progressive multi-component codec (see include/pmc.h).
 // Host code only: argument checks, workspace layout, kernel sequencing, and
 // the per-component metadata of the store.  Every arithmetic step of the path
-// runs in the HIP kernels of kernels.hip.
+// runs in the HIP kernels (the .hip sources).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -576,8 +576,7 @@ pmc_status pmc_compress_static(pmc_ctx* ctx, const pmc_field* f, const void* d_x
   void* ws = scratch_ptr(ctx->device);
   if (!ws) return fail(ctx, PMC_E_DEVICE, "static workspace not set up on device %d", ctx->device);
   // the same kernels as pmc_compress; every workspace word they read is
-  // written first in the same call (the per-component counters are cleared
-  // by a fill kernel), so nothing of an earlier call carries over
+  // written first in the same call, so nothing of an earlier call carries over
   return pmc_compress(ctx, f, d_x, n, tau, ws, PMC_STATIC_WS_BYTES, d_streams, streams_cap, out);
 }
 

@@ -27,7 +27,6 @@ constexpr int kGuard = 8;         // guard planes 2(d+1) for d = 3
 constexpr int kHeaderBytes = 64;  // stream header
 constexpr uint32_t kMagic = 0x31434D50u;
 constexpr int kVersion = 1;
-constexpr int kMaxComponents = 32;
 
 template <class T> struct FT;
 template <> struct FT<float> {
@@ -44,12 +43,6 @@ template <> struct FT<double> {
   static constexpr uint64_t NB = 0xAAAAAAAAAAAAAAAAull;
   static constexpr int RAW_BITS = 2 + kVals * 64;
 };
-
-// capacity of one chunk in 32-bit words: 16 raw blocks (coded blocks are never
-// larger than raw ones, the acceptance rule falls back to raw first)
-template <class T> constexpr int chunk_cap_words() {
-  return (kChunkBlocks * FT<T>::RAW_BITS + 31) / 32;
-}
 
 // ---------------------------------------------------------------------------
 // coefficient order: total sequency lx+ly+lz ascending, ties by local index.

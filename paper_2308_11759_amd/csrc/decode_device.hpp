@@ -18,10 +18,11 @@ namespace pmc {
 // Alg. 2 over one block per lane: x~ = (((x~_in or +0) + x_1) + x_2) ... in
 // the field precision; the block's bits start at its chunk's word offset plus
 // the block's bit offset from the per-block index
+//
 // routes of the inverse transform: kRouteAuto picks per wave (float64: the
 // high-word route where it applies); kRouteFull the plain route; kRouteHi16
 // the float32 high-half route, for components whose every block has p <= 10
-// and fast_dequant(emax) (the caller guarantees it)
+// and hi16_exact(emax) (the caller guarantees it)
 // float64 fields whose blocks qualify decode in 256 registers, two waves per
 // SIMD: kRouteHi16 for the residual components (p <= 10 and hi16_exact(emax)),
 // kRouteFirst for a store's first one (no raw blocks, p <= 26 and emax >= -992).
@@ -196,11 +197,6 @@ __device__ __forceinline__ void stage_span(const uint32_t* payload, const Span& 
   }
 }
 
-// decode the wave's 64 blocks [64 w, 64 w + 64) of a field: x~ = in (or +0)
-// plus components [0, ncomp) of the given streams, left to right.  Every lane
-// runs the component loop (the staging copies are shared); false on a
-// malformed stream.  kFull: every block of the field is full and rows are
-// aligned (all dimensions multiples of 4): no per-lane edge paths.
 // one block of one component, codec 0 (minexp) or codec 1 (step = 2 tau)
 template <class T, int kCodec, int kRoute = kRouteAuto, class R>
 __device__ __forceinline__ bool decode_block_codec(R& r, int minexp, double step, T acc[64], const uint8_t* sq,
@@ -209,6 +205,12 @@ __device__ __forceinline__ bool decode_block_codec(R& r, int minexp, double step
   else return pq_decode_add<T>(r, step, acc);
 }
 
+// decode the wave's 64 blocks [64 w, 64 w + 64) of a field: x~ = in (or +0)
+// plus components [0, ncomp) of the given streams, left to right.  Every lane
+// runs the component loop (the staging copies are shared); false on a
+// malformed stream.  kFull: every block of the field is full and rows are
+// aligned (all dimensions multiples of 4): no per-lane edge paths.  kTile: in
+// and out are the encoder's tiles.
 template <class T, bool kStaged, bool kBox = false, bool kFull = false, int kCodec = 0, bool kHiRes = false, bool kTile = false>
 __device__ __forceinline__ bool decode_wave(const Geo& g, const uint8_t* const* s, const uint32_t* const* aux,
                                             const uint64_t* words, const int* minexp, const double* step, int ncomp,

@@ -10,7 +10,7 @@
 // again instead of held: the residual (x - x~) for every candidate and, in
 // the rare cases that need it there, for the emission.
 //
-// What bounds it: the vector ALUs (3.6 K instructions per wave and component at
+// What bounds it: the vector ALUs (3.8 K instructions per wave and component at
 // 512^3 float32, 1.5 of 2.0 ms), then what two waves per SIMD (float64: one,
 // x alone is 32 KiB of LDS) leave of the LDS latency.  One launch per component
 // with x~ in memory moved 1.73 GB per 512^3 component and ran 8 of them in 3.1
@@ -102,15 +102,15 @@ __device__ __forceinline__ void load_block_lds(gptr<const T> f, const Geo& g, co
 // ---------------------------------------------------------------------------
 // bits of one lane into the wave's window of zeroed LDS words, OR-ed where
 // words are shared with neighbouring lanes.  pos counts from the window's
-// first bit.  kGuard: the wave's span takes several windows, so words outside
+// first bit.  kWindows: the wave's span takes several windows, so words outside
 // this one go to the spare word behind it (a negative position wraps to a
 // large word index).
-template <bool kGuard> struct BitOr {
+template <bool kWindows> struct BitOr {
   uint32_t* buf;
   uint32_t nw;  // words of the window; word nw is spare
   int32_t pos;
   __device__ __forceinline__ void word(uint32_t k, uint32_t v) const {
-    if constexpr (kGuard) k = k < nw ? k : nw;
+    if constexpr (kWindows) k = k < nw ? k : nw;
     atomicOr(&buf[k], v);
   }
   // count <= 64, value holds only its low `count` bits
@@ -149,8 +149,8 @@ __device__ __forceinline__ uint64_t unsqueeze32(uint32_t m, const uint16_t* tab)
 // followed by a positive test, bit 0 is the first test, and a negative test
 // ends the section.  When the last significant coefficient is coefficient 63
 // its terminator is implied and the section ends just before it.
-template <bool kGuard>
-__device__ __forceinline__ void plane_emit(BitOr<kGuard>& w, uint64_t wd, uint32_t& n, const uint16_t* tab) {
+template <bool kWindows>
+__device__ __forceinline__ void plane_emit(BitOr<kWindows>& w, uint64_t wd, uint32_t& n, const uint16_t* tab) {
   if (n > 0) w.put((wd << (64u - n)) >> (64u - n), n);
   if (n >= 64) return;
   const uint64_t rest = wd >> n;
@@ -264,8 +264,8 @@ __device__ __forceinline__ uint32_t planes_cost(const U v[64], int zl, int p, ui
 }
 
 // emit planes [b, min(p, base + W)) of a group whose plane words are in G
-template <int W, bool kGuard>
-__device__ __forceinline__ void group_emit(BitOr<kGuard>& w, uint32_t G[2 * W], int base, int b, int p, uint32_t& n,
+template <int W, bool kWindows>
+__device__ __forceinline__ void group_emit(BitOr<kWindows>& w, uint32_t G[2 * W], int base, int b, int p, uint32_t& n,
                                            const uint16_t* tab) {
 #pragma unroll 1
   for (int t = base; t < base + W && t < p; ++t) {
@@ -278,8 +278,8 @@ __device__ __forceinline__ void group_emit(BitOr<kGuard>& w, uint32_t G[2 * W], 
   }
 }
 // emit planes [zl, p) from the coefficients
-template <bool kGuard, class U>
-__device__ __forceinline__ void planes_emit(BitOr<kGuard>& w, const U v[64], int zl, int p, const uint16_t* tab) {
+template <bool kWindows, class U>
+__device__ __forceinline__ void planes_emit(BitOr<kWindows>& w, const U v[64], int zl, int p, const uint16_t* tab) {
   constexpr int P = 8 * (int)sizeof(U), W = 8;
   uint32_t n = 0;
   w.pos += zl;

@@ -24,8 +24,8 @@ namespace pmc {
 // (256^3 float32, 8 components: 218 us, 304 with L = 8; the upload of such a
 // store takes 3 ms).  One launch per component with 64 chunks per wave read
 // from global memory had 51 waves in flight for 3 M values and took 145 us per
-// component; all 6 take 91 us now.  L = 64: unstaged, for an index whose chunks are longer than any
-// encoder writes (which a loader may still be given).
+// component; all 6 take 79 us now.  L = 64: unstaged, for an index whose chunks
+// are longer than any encoder writes (which a loader may still be given).
 template <class T, int kCodec, class R>
 __device__ __forceinline__ void aux_chunk(const AuxArgs& a, int comp, uint64_t chunk, R& r, uint32_t from, bool ok,
                                           const uint8_t* sq) {
@@ -96,8 +96,8 @@ __device__ __forceinline__ unsigned long long ordered(double v) {
 // min / max over the finite samples and the count of the others.  Keys are
 // the samples' bits mapped to unsigned integers of the same order (sign and
 // zero sign included), so the reduction is exact integer min / max in the
-// field's own width; the per-wave result is widened to the double key of the
-// same value for the device-wide atomics.  16-byte loads when aligned.
+// field's own width; a workgroup's result is widened to the double key of the
+// same value, for the host to combine.  16-byte loads when aligned.
 template <class T> struct RangeKey;
 template <> struct RangeKey<float> {
   typedef uint32_t K;
@@ -210,10 +210,10 @@ __global__ __launch_bounds__(kRangeThreads) void k_range(const T* __restrict__ x
   }
 }
 
-// p[0, n) = v, except p[j] = vj (j >= n: none)
-__global__ void k_fill64(unsigned long long* p, uint64_t n, unsigned long long v, uint64_t j, unsigned long long vj) {
+// p[0, n) = v
+__global__ void k_fill64(unsigned long long* p, uint64_t n, unsigned long long v) {
   uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = i == j ? vj : v;
+  if (i < n) p[i] = v;
 }
 
 // ---------------------------------------------------------------------------
@@ -387,12 +387,8 @@ template <class T> hipError_t launch_range(const T* x, uint64_t n, unsigned long
   return hipGetLastError();
 }
 hipError_t launch_fill64(unsigned long long* p, uint64_t n, unsigned long long v, hipStream_t s) {
-  return launch_fill64_one(p, n, v, n, v, s);
-}
-hipError_t launch_fill64_one(unsigned long long* p, uint64_t n, unsigned long long v, uint64_t j,
-                             unsigned long long vj, hipStream_t s) {
   if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_fill64, dim3((uint32_t)((n + 255) / 256)), dim3(256), 0, s, p, n, v, j, vj);
+  hipLaunchKernelGGL(k_fill64, dim3((uint32_t)((n + 255) / 256)), dim3(256), 0, s, p, n, v);
   return hipGetLastError();
 }
 

@@ -105,9 +105,6 @@ template <class T> struct DecArgs {
   unsigned int* status;  // bit 0: malformed stream
 };
 
-// a box [lo, hi) of the field (value coordinates x, y, z) for region
-// retrieval: blo/bhi are its block ranges; the output is the box alone, dense,
-// x fastest.  Work: one workgroup per (block row of the box, wave of that row)
 // a launch with one wave per component: where each component's words are
 // staged in the workgroup's LDS (word offset, and words it holds)
 constexpr int kMaxSplit = 8, kMaxSplit64 = 4;  // (4: float64 that is not hires)
@@ -115,6 +112,9 @@ struct SplitArgs {  // (launch_decode, launch_decode_box: null for one wave over
   uint32_t base[kMaxSplit], cap[kMaxSplit];
   uint32_t lds_bytes;
 };
+// a box [lo, hi) of the field (value coordinates x, y, z) for region
+// retrieval: blo/bhi are its block ranges; the output is the box alone, dense,
+// x fastest.  Work: one workgroup per (block row of the box, wave of that row)
 struct BoxArgs {
   uint64_t lo[3], hi[3];
   uint64_t blo[3], bhi[3];
@@ -207,9 +207,6 @@ uint32_t range_groups(uint64_t n, uint64_t max_groups);
 template <class T>
 hipError_t launch_range(const T* x, uint64_t n, unsigned long long* out, uint32_t groups, hipStream_t s);
 hipError_t launch_fill64(unsigned long long* p, uint64_t n, unsigned long long v, hipStream_t s);
-// the same with p[j] = vj instead (one launch)
-hipError_t launch_fill64_one(unsigned long long* p, uint64_t n, unsigned long long v, uint64_t j,
-                             unsigned long long vj, hipStream_t s);
 // out[0] = sum of d, out[1] = sum of d^2 in float64, d = a - b - shift (b NULL: 0);
 // ws holds sum_sq_ws_bytes() bytes of partials; out may lie inside ws past them
 template <class T>
@@ -221,7 +218,8 @@ template <class T>
 hipError_t launch_cast_encode(const T* x, uint64_t N, int n, float* comps, unsigned long long* linf, hipStream_t s);
 template <class T> hipError_t launch_cast_decode(const float* comps, uint64_t N, int k, T* out, hipStream_t s);
 
-// capacity of one chunk's staging slot in 32-bit words
+// capacity of one chunk in 32-bit words: 16 raw blocks (coded ones are never
+// larger, the acceptance rule falls back to raw first)
 inline uint64_t chunk_cap_words_host(int dtype) {
   const uint64_t raw = dtype == 1 ? 2 + 64 * 32 : 2 + 64 * 64;
   return (16 * raw + 31) / 32;
