@@ -128,8 +128,9 @@ template <> struct RangeKey<double> {
 // same two words with atomics, which one cache line serialises (about 10 ns
 // each).  One plain store per workgroup, no more workgroups than CUs and 16
 // waves in each to keep the loads in flight take the whole call down by 15 us
-// for 64^3 float64, 50 us for 9.2 M float32 values and 11 us for 512^3 (118 to
-// 107 us, 5.0 TB/s, the rate a large copy reaches).
+// for 64^3 float64, 50 us for 9.2 M float32 values and 10 us for 512^3 (118 to
+// 108 us, 5.0 TB/s, the rate a large copy reaches; two workgroups per CU 111,
+// 512^3 float64 196 and 203).
 constexpr uint32_t kRangeThreads = 1024;
 template <class T>
 __global__ __launch_bounds__(kRangeThreads) void k_range(const T* __restrict__ x, uint64_t n,

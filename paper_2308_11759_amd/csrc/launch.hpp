@@ -202,7 +202,7 @@ uint64_t stage_words();  // capacity of the decoder's LDS staging buffer, in wor
 // min / max / non-finite count of n samples: one partial of kRangeWords words
 // per workgroup at out; range_groups: how many workgroups suit n, at most
 // max_groups
-constexpr uint32_t kRangeWords = 3, kRangeGroups = 512;
+constexpr uint32_t kRangeWords = 3, kRangeGroups = 256;
 uint32_t range_groups(uint64_t n, uint64_t max_groups);
 template <class T>
 hipError_t launch_range(const T* x, uint64_t n, unsigned long long* out, uint32_t groups, hipStream_t s);
