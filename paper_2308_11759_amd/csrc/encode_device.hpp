@@ -775,9 +775,12 @@ typedef __attribute__((address_space(4))) const FieldJob CFieldJob;
 // The job of a single field comes as the kernel's argument, read (as a batch's
 // table is) through the constant address space, so that its values are loaded
 // where they are needed instead of being held across the wave's work.
-// (codec 1's residual, integers and x~ take 380 registers: two waves per SIMD
-// spill 130 of them and are no faster, 0.38 ms per 256^3 float32 and 8
-// components either way)
+// (codec 1's residual, integers and x~ take 380 registers in float32: two waves
+// per SIMD spill 130 of them and are no faster, 0.38 ms per 256^3 and 8
+// components either way.  In float64 they spill 235 of 512, 900 bytes of scratch
+// per lane; a compression of 256^3 takes 1.03 ms all the same, 1.69 with a
+// launch per component, which spilled none.  Codec 0 spills 64 registers, with
+// edge paths 96, in float64 146 and 232, in batches 72 and 245.)
 template <class T, bool kFull, int kCodec>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && kCodec == 0 ? 2 : 1))) void k_encode(
     FieldJob) {
